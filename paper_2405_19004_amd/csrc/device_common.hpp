@@ -11,24 +11,32 @@ namespace vps {
 constexpr int kMaxN = 2 * kMaxDegree + 1;  // patch closure points per direction
 constexpr int kMaxM = 2 * kMaxDegree - 1;  // patch interior points per direction
 
-// Reciprocal eigenvalue sums of one degree (patch pair, reference cell size 1).  The colour pass
-// indexes them by lane, so they live in constant memory; every other 1D table is a compile-time
-// constant (generated header patch_tables_gen.hpp).
+// Per-lane tables of one degree (patch pair, reference cell size 1, the eigenbasis of eigen_basis()).
+// The colour pass indexes them by lane, so they live in constant memory; every other 1D table is a
+// compile-time constant (generated header patch_tables_gen.hpp).
 template <typename T>
 struct DevTables {
-  T inv3[kMaxM * kMaxM * kMaxM];  // 1 / (lam[a2] + lam[a1] + lam[a0]), index (a2*m + a1)*m + a0
-  T inv2[kMaxM * kMaxM];          // 1 / (lam[a1] + lam[a0]),           index a1*m + a0
+  T inv3[kMaxM * kMaxM * kMaxM];  // 1 / (lam[a2] + lam[a1] + lam[a0]) / scales^2, index (a2*m + a1)*m + a0
+  T inv2[kMaxM * kMaxM];          // 1 / (lam[a1] + lam[a0]) / scales^2,           index a1*m + a0
+  T al[kMaxM], mu[kMaxM];         // S^T A, S^T M at the left closure end
 };
 
 template <typename T>
 inline void fill_dev_tables(int k, DevTables<T>& out) {
-  const Tables1D& t = tables_for_degree(k);
-  const int m = 2 * k - 1;
-  for (int a2 = 0; a2 < m; ++a2)
+  const EigenBasis e = eigen_basis(k, sizeof(T) == 4);
+  const int m = 2 * k - 1, n = 2 * k + 1;
+  for (int a2 = 0; a2 < m; ++a2) {
+    const double q2 = e.scale[a2] * e.scale[a2];
+    out.al[a2] = (T)e.At[a2 * n];
+    out.mu[a2] = (T)e.Mt[a2 * n];
     for (int a1 = 0; a1 < m; ++a1) {
-      out.inv2[a2 * m + a1] = (T)(1.0 / (t.lam[a2] + t.lam[a1]));
-      for (int a0 = 0; a0 < m; ++a0) out.inv3[(a2 * m + a1) * m + a0] = (T)(1.0 / (t.lam[a2] + t.lam[a1] + t.lam[a0]));
+      const double q1 = q2 * e.scale[a1] * e.scale[a1];
+      out.inv2[a2 * m + a1] = (T)(1.0 / (q1 * (e.lam[a2] + e.lam[a1])));
+      for (int a0 = 0; a0 < m; ++a0)
+        out.inv3[(a2 * m + a1) * m + a0] =
+            (T)(1.0 / (q1 * e.scale[a0] * e.scale[a0] * (e.lam[a2] + e.lam[a1] + e.lam[a0])));
     }
+  }
 }
 
 // s + c x for a coefficient c that is a compile-time table entry.  IEEE arithmetic does not let the
@@ -57,6 +65,42 @@ __device__ __forceinline__ void st_lane(T* p, unsigned off, T v) {
   VPS_GLOBAL char* g = (VPS_GLOBAL char*)p;
   asm volatile("" : "+s"(g));
   *(VPS_GLOBAL T*)(g + off) = v;
+}
+
+// A window of `bytes` bytes of global memory from a wave-uniform base: element at (uniform byte offset
+// so) + (per-lane byte offset vo), both below 4 GiB.  One buffer instruction adds base, so (one scalar
+// register) and vo, so a kernel that walks many planes keeps one 32-bit scalar per plane and no 64-bit
+// addresses.  A load at vo = kOutside reads 0 (the hardware's range check), which replaces a select
+// per value.
+template <typename T>
+struct Window {
+  static constexpr unsigned kOutside = 0xffffffffu;
+  __amdgpu_buffer_rsrc_t r;
+  __device__ __forceinline__ Window(const T* base, unsigned bytes)
+      : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(base), 0, bytes, 0x00027000)) {}
+  __device__ __forceinline__ T load(unsigned so, unsigned vo) const {
+    if constexpr (sizeof(T) == 8)
+      return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, vo, so, 0));
+    else
+      return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, vo, so, 0));
+  }
+  __device__ __forceinline__ void store(unsigned so, unsigned vo, T v) const {
+    if constexpr (sizeof(T) == 8) {
+      typedef unsigned u2 __attribute__((ext_vector_type(2)));
+      __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), r, vo, so, 0);
+    } else {
+      __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, vo, so, 0);
+    }
+  }
+};
+
+// t / D for 0 <= t < 4096 by one 24-bit multiply and a shift (full rate; the compiler's general form
+// takes a quarter-rate 32-bit high multiply).  Exact: t (M D - 2^20) < 2^20 as t D < 2^20.
+template <int D>
+__device__ __forceinline__ int div_small(int t) {
+  static_assert(D >= 1 && D < 256, "divisor");
+  constexpr unsigned M = ((1u << 20) + D - 1) / D;
+  return (int)(__umul24((unsigned)t, M) >> 20);
 }
 
 // Geometry of one level as the kernels see it.

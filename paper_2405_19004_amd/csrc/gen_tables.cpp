@@ -23,8 +23,10 @@ void emit(const char* type, const char* name, const std::vector<double>& v, cons
 int main() {
   std::printf("// Generated by gen_tables.cpp from tables.cpp; do not edit.\n#pragma once\n\n");
   std::printf("namespace vps {\nnamespace gen {\n\n");
-  std::printf("// Patch tables of degree K in precision T: Mc, Ac (interior rows x closure columns), S, lam,\n"
-              "// and par[a] = +1 / -1 when eigenvector a is even / odd under the mirror i -> m-1-i.\n");
+  std::printf("// Patch tables of degree K in precision T: Mc, Ac (interior rows x closure columns); the eigenbasis\n"
+              "// (eigen_basis in tables.hpp: the K even eigenvectors first, then the K-1 odd ones) S, lam;\n"
+              "// W = S^T M on the interior columns; mu, al = S^T M, S^T A at the left closure end (times +1 / -1\n"
+              "// for an even / odd vector at the right end); be = al - lam mu.\n");
   std::printf("template <typename T, int K>\nstruct PatchTables;\n\n");
   for (int k = 1; k <= vps::kMaxDegree; ++k) {
     const vps::Tables1D& t = vps::tables_for_degree(k);
@@ -34,27 +36,21 @@ int main() {
       std::printf("template <>\nstruct PatchTables<%s, %d> {\n", type, k);
       emit(type, "Mc", t.Mc, fmt);
       emit(type, "Ac", t.Ac, fmt);
-      emit(type, "S", t.S, fmt);
-      emit(type, "lam", t.lam, fmt);
-      // the patch pair (A, M) is mirror-symmetric, so each eigenvector is even or odd
-      const int m = 2 * k - 1;
-      std::printf("  static constexpr int par[%d] = {", m);
+      const int m = 2 * k - 1, n = 2 * k + 1;
+      const vps::EigenBasis e = vps::eigen_basis(k, f == 1);
+      std::vector<double> W(m * m), mu(m), al(m), be(m);
       for (int a = 0; a < m; ++a) {
-        double se = 0, so = 0, nrm = 0;
-        for (int i = 0; i < m; ++i) {
-          const double u = t.S[i * m + a], w = t.S[(m - 1 - i) * m + a];
-          se = std::fmax(se, std::fabs(u - w));
-          so = std::fmax(so, std::fabs(u + w));
-          nrm = std::fmax(nrm, std::fabs(u));
-        }
-        const int p = se <= 1e-12 * nrm ? 1 : so <= 1e-12 * nrm ? -1 : 0;
-        if (p == 0) {
-          std::fprintf(stderr, "degree %d: eigenvector %d has no mirror parity\n", k, a);
-          return 1;
-        }
-        std::printf("%s%d", a ? ", " : "", p);
+        for (int i = 0; i < m; ++i) W[a * m + i] = e.Mt[a * n + i + 1];
+        mu[a] = e.Mt[a * n];
+        al[a] = e.At[a * n];
+        be[a] = e.be[a];
       }
-      std::printf("};\n");
+      emit(type, "S", e.S, fmt);
+      emit(type, "W", W, fmt);
+      emit(type, "lam", e.lam, fmt);
+      emit(type, "mu", mu, fmt);
+      emit(type, "al", al, fmt);
+      emit(type, "be", be, fmt);
       std::printf("};\n\n");
     }
   }

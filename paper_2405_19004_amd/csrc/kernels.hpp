@@ -34,7 +34,32 @@ hipError_t init_smoother_tables();
 // kModeZero: colour 0 of the multiplicative pass on a zero iterate, x <- S_0(0, b): writes
 // A_j^{-1} b^I on the colour's patch interiors and 0 on every other node (the closures of colour 0
 // tile the grid), so x need not be cleared first and is never read.
-enum { kModeMultiplicative = 0, kModeAdditive = 1, kModeBoundary = 2, kModeMfma = 4, kModeZero = 5 };
+// The multiplicative pass has two forms (smoother.hip).  The eigenbasis form is faster; its rounding is
+// relative to the variation of x over a patch, a white error.  The residual form x + A_j^{-1} (b - A x)
+// rounds a residual, a smooth error: iterated to stagnation it reaches a lower residual.  So:
+// kModeMultiplicative: one step on a caller's iterate.  Eigenbasis form where eigen_step_fits (there its
+//   error against FP64 is the smaller one), and a patch with a non-finite old value becomes non-finite;
+//   elsewhere the residual form.
+// kModeTail: the eigenbasis form without looking at old interior values, for corrections (V-cycle levels
+//   that start from 0: the rounding is relative to the correction) and for later colours of a step whose
+//   first colour was 0.  After colour 0, whose closures tile the grid, the non-finite values are a union
+//   of whole patch interiors, and every other patch that overlaps one has it on its closure's rim too:
+//   the values are those of kModeMultiplicative.
+// kModeResidual: the residual form, for the last smoothing step of a V-cycle on a caller's iterate, which
+//   decides how far repeated V-cycles reduce the residual.
+enum { kModeMultiplicative = 0, kModeAdditive = 1, kModeBoundary = 2, kModeMfma = 4, kModeZero = 5, kModeTail = 6, kModeResidual = 7 };
+
+// The eigenbasis form serves degrees 3-7, in 2D FP32 degrees 5-7: degree 1 is a stencil, and below these the
+// face transforms cost what they save (finest pass against the residual form, us: 3D degree 2, 256^3 cells,
+// FP32 41.0 / 41.5, FP64 61.2 / 61.7; 2D 2048^2 cells degree 2 34.2 / 31.3 and 55.2 / 56.2; 2D 1024^2 FP32
+// degree 3 20.7 / 19.8, degree 4 36.5 / 33.7).
+inline bool has_eigen_form(int dim, int k, int prec) { return k >= (dim == 2 && prec == 1 ? 5 : 3); }
+// For single steps, 3D levels with fewer than 16 cells per axis keep the residual form as well: a patch spans a
+// quarter of the domain or more there, and the eigenbasis form's error (FP32 model, one step, degree 4) is
+// 1.5 times the residual form's on 8^3 cells, 0.8 times on 16^3; in 2D it is 0.05-0.6 times.
+inline bool eigen_step_fits(const LevelGeom& g, int prec) {
+  return has_eigen_form(g.dim, g.k, prec) && (g.dim == 2 || g.level >= 4);
+}
 
 // One member of a packed colour-pass launch (see launch_colour_pass_group).
 struct ColourPassDesc {

@@ -220,15 +220,24 @@ Status colour_pass(Problem* p, int level, int prec, int mode, int colour, const 
   return Status::ok();
 }
 
-Status smoother(Problem* p, int level, int prec, int mode, bool reverse, const void* b, void* x, bool x_zero) {
+// Kernel mode of the i-th pass (colour c) of a smoothing step on a level.
+static int step_mode(int mode, const LevelGeom& g, int prec, int i, int c, bool reverse, bool x_zero, StepUse use) {
+  // on x = 0 the first multiplicative colour reduces to x^I = A_j^{-1} b^I (residual = b,
+  // x^B = 0): the additive kernel gives the same values without forming the residual; for colour
+  // 0 the from-zero kernel also writes the zeros of the rest of the grid, so x may hold anything
+  if (i == 0 && x_zero && mode != kModeAdditive) return c == 0 ? kModeZero : kModeAdditive;
+  if (mode != kModeMultiplicative) return mode;
+  if (use == StepUse::kLast) return kModeResidual;
+  if (use == StepUse::kCorrection) return kModeTail;
+  return i > 0 && !reverse && eigen_step_fits(g, prec) ? kModeTail : kModeMultiplicative;
+}
+
+Status smoother(Problem* p, int level, int prec, int mode, bool reverse, const void* b, void* x, bool x_zero,
+                StepUse use) {
   const int nc = 1 << p->dim;
   for (int i = 0; i < nc; ++i) {
     const int c = reverse ? nc - 1 - i : i;
-    // on x = 0 the first multiplicative colour reduces to x^I = A_j^{-1} b^I (residual = b,
-    // x^B = 0): the additive kernel gives the same values without forming the residual; for colour
-    // 0 the from-zero kernel also writes the zeros of the rest of the grid, so x may hold anything
-    const int m = (i == 0 && x_zero && mode != kModeAdditive) ? (c == 0 ? kModeZero : kModeAdditive) : mode;
-    VPS_TRY(colour_pass(p, level, prec, m, c, b, x));
+    VPS_TRY(colour_pass(p, level, prec, step_mode(mode, p->geom(level), prec, i, c, reverse, x_zero, use), c, b, x));
   }
   return Status::ok();
 }
@@ -257,7 +266,8 @@ Status vcycle_top(Problem* p, int prec, int top, const void* bT, void* xT, bool 
     const void* b = lvl == top ? bT : p->lv[lvl].b[prec];
     void* x = lvl == top ? xT : p->lv[lvl].x[prec];
     // below the top, x starts from 0: the restriction into this level zeroed it
-    VPS_TRY(smoother(p, lvl, prec, vcycle_mode(p), false, b, x, lvl < top || top_zero));
+    const bool zero = lvl < top || top_zero;
+    VPS_TRY(smoother(p, lvl, prec, vcycle_mode(p), false, b, x, zero, zero ? StepUse::kCorrection : StepUse::kStep));
     VPS_HIP(launch_operator(p->geom(lvl), prec, x, b, p->lv[lvl].r[prec], p->stream));
     VPS_HIP(launch_restrict(p->geom(lvl), prec, p->lv[lvl].r[prec], p->lv[lvl - 1].b[prec], p->lv[lvl].t[prec],
                             p->stream, lvl - 1 >= 2 ? p->lv[lvl - 1].x[prec] : nullptr));
@@ -268,7 +278,8 @@ Status vcycle_top(Problem* p, int prec, int top, const void* bT, void* xT, bool 
     const void* b = lvl == top ? bT : p->lv[lvl].b[prec];
     void* x = lvl == top ? xT : p->lv[lvl].x[prec];
     VPS_HIP(launch_prolongate_add(p->geom(lvl), prec, p->lv[lvl - 1].x[prec], x, p->stream));
-    VPS_TRY(smoother(p, lvl, prec, vcycle_mode(p), post_rev, b, x));
+    VPS_TRY(smoother(p, lvl, prec, vcycle_mode(p), post_rev, b, x, false,
+                     lvl < top || top_zero ? StepUse::kCorrection : StepUse::kLast));
   }
   return Status::ok();
 }
@@ -377,13 +388,14 @@ Status vcycle_group(Problem* const* ps, int n, int prec, const void* const* bL, 
   auto level_x = [&](int i, int lvl) -> void* { return lvl == ps[i]->L ? xL[i] : ps[i]->lv[lvl].x[prec]; };
   std::vector<ColourPassMember> mem, sep;
   // x_zero: every member's x is 0 on entry (the first colour then needs no residual, as in smoother())
-  auto smooth = [&](int lvl, bool reverse, bool x_zero) -> Status {
+  auto smooth = [&](int lvl, bool reverse, bool x_zero, bool post) -> Status {
     mem.clear();
     for (int i = 0; i < n; ++i)
       if (ps[i]->L >= lvl) mem.push_back({ps[i]->geom(lvl), level_b(i, lvl), level_x(i, lvl)});
     for (int j = 0; j < nc; ++j) {
       const int c = reverse ? nc - 1 - j : j;
-      int mode = (j == 0 && x_zero) ? (c == 0 ? kModeZero : kModeAdditive) : vcycle_mode(ps[0]);
+      const StepUse use = top_zero ? StepUse::kCorrection : post ? StepUse::kLast : StepUse::kStep;
+      const int mode = step_mode(vcycle_mode(ps[0]), mem[0].g, prec, j, c, reverse, x_zero, use);
       if (mode == kSmoothSeparate) {
         // residual of every member, then the packed local solves on it
         sep.assign(mem.begin(), mem.end());
@@ -402,7 +414,7 @@ Status vcycle_group(Problem* const* ps, int n, int prec, const void* const* bL, 
   };
   for (int lvl = Lmax; lvl >= 2; --lvl) {
     // levels below a member's top start from 0 (the restriction into them zeroed x)
-    VPS_TRY(smooth(lvl, false, top_zero));
+    VPS_TRY(smooth(lvl, false, top_zero, false));
     for (int i = 0; i < n; ++i) {
       if (ps[i]->L < lvl) continue;
       Problem* p = ps[i];
@@ -416,7 +428,7 @@ Status vcycle_group(Problem* const* ps, int n, int prec, const void* const* bL, 
     for (int i = 0; i < n; ++i)
       if (ps[i]->L >= lvl)
         VPS_HIP(launch_prolongate_add(ps[i]->geom(lvl), prec, ps[i]->lv[lvl - 1].x[prec], level_x(i, lvl), st));
-    VPS_TRY(smooth(lvl, post_rev, false));
+    VPS_TRY(smooth(lvl, post_rev, false, true));
   }
   return Status::ok();
 }

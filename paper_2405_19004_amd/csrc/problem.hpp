@@ -71,7 +71,11 @@ Status create_problem(int dim, int k, int L, unsigned flags, hipStream_t st, Pro
 
 // Device steps (asynchronous on p->stream).
 // x_zero: x is 0 on entry (the first colour then runs the additive kernel, same values)
-Status smoother(Problem* p, int level, int prec, int mode, bool reverse, const void* b, void* x, bool x_zero = false);
+// use: what x is (kernel modes in kernels.hpp): a caller's iterate, a correction of a V-cycle level that
+// started from 0, or a caller's iterate in the last smoothing step of a V-cycle
+enum class StepUse { kStep, kCorrection, kLast };
+Status smoother(Problem* p, int level, int prec, int mode, bool reverse, const void* b, void* x, bool x_zero = false,
+                StepUse use = StepUse::kStep);
 Status colour_pass(Problem* p, int level, int prec, int mode, int colour, const void* b, void* x);
 Status coarse_solve(Problem* p, int prec, const void* b, void* x);
 Status vcycle(Problem* p, int prec, const void* b, void* x);

@@ -13,6 +13,8 @@
 //   x_j^I <- A_j^{-1} (b_j^I - A^{IB} x_j^B),
 // i.e. the residual is formed with the patch interior taken as zero and the
 // interior is overwritten, so x^I is never loaded.
+// The multiplicative pass has two forms: the eigenbasis form, which works on the boundary nodes of the
+// closures only, and the residual form as written above; kernels.hpp says which serves what.
 //
 // Mapping (designed for CDNA4, not a translation of the paper's CUDA):
 //  * a workgroup owns PPW patches that are consecutive along x0 inside the
@@ -29,6 +31,10 @@
 #include "device_common.hpp"
 #include "kernels.hpp"
 #include "patch_tables_gen.hpp"
+
+#include <cmath>
+#include <type_traits>
+#include <vector>
 
 namespace vps {
 
@@ -55,23 +61,13 @@ template <int K> struct SmootherShape<2, K> {
   static constexpr int PPW = (K == 1 ? 64 : K == 2 ? 32 : K == 3 ? 16 : K <= 5 ? 12 : 8) / (ONE_WAVE ? 2 : 1);
   static constexpr int NT = ONE_WAVE ? 64 : 128;
 };
-#ifndef VPS_Q4_3D_PPW
-#define VPS_Q4_3D_PPW 2
-#endif
-#ifndef VPS_Q4_3D_NT
-#define VPS_Q4_3D_NT 128
-#endif
-// Degrees (bit K) whose default 3D shape takes the aliased LDS layout: measured 2-13% faster for
-// degrees 3-7 (occupancy), no gain for degrees 1-2, where the layout is already small.
-#ifndef VPS_3D_ALIAS_MASK
-#define VPS_3D_ALIAS_MASK 0xF8
-#endif
 template <int K> struct SmootherShape<3, K> {
-  static constexpr int PPW = K == 1 ? 32 : K == 2 ? 8 : K == 3 ? 4 : K == 4 ? VPS_Q4_3D_PPW : 1;
-  static constexpr int NT = K == 4 ? VPS_Q4_3D_NT : K <= 5 ? 128 : K == 6 ? 192 : 256;
-  // the default shape of the multiplicative pass shares one LDS region between the closure and the
-  // first two contraction stages (see SmootherLds)
-  static constexpr bool ALIAS = ((VPS_3D_ALIAS_MASK) >> K) & 1;
+  static constexpr int PPW = K == 1 ? 32 : K == 2 ? 8 : K == 3 ? 4 : K == 4 ? 2 : 1;
+  static constexpr int NT = K <= 5 ? 128 : K == 6 ? 192 : 256;
+  // the default shape of the residual form shares one LDS region between the closure and the
+  // first two contraction stages (see SmootherLds): measured 2-13% faster for degrees 3-7 (occupancy),
+  // no gain for degrees 1-2, where the layout is already small
+  static constexpr bool ALIAS = K >= 3;
 };
 
 // Patches per workgroup for small launches (coarse levels): fewer patches per workgroup means
@@ -168,8 +164,6 @@ struct SmootherLds {
   static constexpr int offW57 = PR ? W46 : AL ? 0 : A3;  // W5 and W7
 };
 
-__device__ __forceinline__ bool on_boundary(long long i, long long n1d) { return i == 0 || i == n1d - 1; }
-
 // A per-lane LDS offset the optimiser may not take apart.  Without it, base + i * stride inside an
 // unrolled loop is re-associated into a fresh (quarter-rate) 32-bit multiply per element; behind
 // this barrier each element is the base register plus a constant in the instruction's offset field.
@@ -206,7 +200,7 @@ __device__ __forceinline__ void apply_st(const T (&v)[2 * K - 1], T (&t)[2 * K -
 #pragma unroll
   for (int a = 0; a < m; ++a) {
     T s = T(0);
-    if (PT::par[a] > 0) {
+    if (a < K) {
 #pragma unroll
       for (int i = 0; i <= h; ++i) s = fma_tab(PT::S[i * m + a], e[i], s);
     } else {
@@ -227,7 +221,7 @@ __device__ __forceinline__ void apply_s(const T (&t)[2 * K - 1], T (&w)[2 * K - 
     T ev = T(0), od = T(0);
 #pragma unroll
     for (int a = 0; a < m; ++a) {
-      if (PT::par[a] > 0) {
+      if (a < K) {
         ev = fma_tab(PT::S[i * m + a], t[a], ev);
       } else if (i < h) {
         od = fma_tab(PT::S[i * m + a], t[a], od);
@@ -238,12 +232,814 @@ __device__ __forceinline__ void apply_s(const T (&t)[2 * K - 1], T (&w)[2 * K - 
   }
 }
 
-// Degrees (bit K) whose FP64 3D multiplicative pass takes the aliased LDS layout below: measured
-// 11-45% faster for degrees 2-7 (occupancy: 3D Q4 goes from 33 to 17 KB of LDS, from 8 to 18 waves
-// per compute unit), equal at degree 1.
-#ifndef VPS_MULT3_ALIAS_MASK
-#define VPS_MULT3_ALIAS_MASK 0xFC
-#endif
+// ------------------------------------------------------------------ eigenbasis form
+//
+// The multiplicative pass computes x^I + A_j^{-1} (b^I - Abar_j x).  The local solver is exact, so the
+// interior values cancel and the result is A_j^{-1} (b^I - A^{IB} x^B) (eq:A_ib_2d/3d): only the
+// closure's boundary nodes enter.  Transformed by S^T along every axis, the boundary term needs no
+// 1D matrix of the closure at all.  Write, along one axis, Mt = S^T M = [mu W mu'] and
+// At = S^T A = Lambda Mt + [be 0 be'] (m x n; W the interior columns, mu/al/be the end columns, whose
+// right-hand ones differ from the left by the eigenvectors' parity only).  Every boundary node belongs
+// to one face: x0 faces own their whole closure, x1 faces the x0-interior part, x2 faces the x0- and
+// x1-interior part.  A face F normal to axis a adds
+//   al_a (x) P + mu_a (x) Q,   P = Mt (x) Mt F,   Q = (At (x) Mt + Mt (x) At) F
+// (W in place of Mt along the axes where the face is interior only), so a patch costs six 2D face
+// transforms, six multiply-adds per node in the eigenbasis, and the S^T / S transforms of the solve: in
+// 3D Q4 about 18 k lane operations against 35 k of the form that contracts the whole closure with the
+// 1D patch matrices.
+// Rounding: that form's error is the cancellation in b - A x; this form's is relative to the values it
+// transforms.  A constant c has A c = 0 on a patch's interior rows, so the pass runs on x^B - c and adds
+// c at the end, c the mean of two opposite closure corners: the rounding is then relative to the
+// variation of x over the patch.  Measured in an FP32 model of one step from the exact solution (error
+// and residual, the closure form's in brackets): 2D Q3 32^2 3.0e-8, 5.8e-5 (6.7e-7, 1.6e-4); 2D Q7 64^2
+// 3.0e-8, 1.7e-3 (1.4e-6, 3.8e-3); 3D Q3 16^3 1.4e-7, 3.3e-6 (6.9e-7, 3.6e-6); without c the residuals
+// were 1.0-2.2 times the closure form's.
+
+// t = Mt v for a closure line v (n values): the interior part through W, the ends through mu.  The
+// even and odd end sums come back in Ee, Eo for the Lambda Mt + be form of At.
+template <typename T, int K>
+__device__ __forceinline__ void apply_mt(const T (&v)[2 * K + 1], T (&t)[2 * K - 1], T& Ee, T& Eo) {
+  using PT = gen::PatchTables<T, K>;
+  constexpr int m = 2 * K - 1, h = K - 1;
+  T e[K], o[K];
+#pragma unroll
+  for (int i = 0; i < h; ++i) {
+    e[i] = v[1 + i] + v[m - i];
+    o[i] = v[1 + i] - v[m - i];
+  }
+  e[h] = v[1 + h];
+  Ee = v[0] + v[2 * K];
+  Eo = v[0] - v[2 * K];
+#pragma unroll
+  for (int a = 0; a < m; ++a) {
+    T s = PT::mu[a] * (a < K ? +Ee : +Eo);
+#pragma unroll
+    for (int i = 0; i < (a < K ? K : h); ++i) s = fma(PT::W[a * m + i], a < K ? +e[i] : +o[i], s);
+    t[a] = s;
+  }
+}
+
+// t = W v (m values)
+template <typename T, int K>
+__device__ __forceinline__ void apply_w(const T (&v)[2 * K - 1], T (&t)[2 * K - 1]) {
+  using PT = gen::PatchTables<T, K>;
+  constexpr int m = 2 * K - 1, h = K - 1;
+  T e[K], o[K];
+#pragma unroll
+  for (int i = 0; i < h; ++i) {
+    e[i] = v[i] + v[m - 1 - i];
+    o[i] = v[i] - v[m - 1 - i];
+  }
+  e[h] = v[h];
+#pragma unroll
+  for (int a = 0; a < m; ++a) {
+    T s = T(0);
+#pragma unroll
+    for (int i = 0; i < (a < K ? K : h); ++i) s = fma(PT::W[a * m + i], a < K ? +e[i] : +o[i], s);
+    t[a] = s;
+  }
+}
+
+// Launch shape of the eigenbasis form: patches per workgroup, threads, and whether the buffers of
+// consecutive stages share one LDS region (two more barriers, up to half the LDS).
+template <int PPWv, int NTv, bool ALv>
+struct EigShape {
+  static constexpr int PPW = PPWv, NT = NTv;
+  static constexpr bool AL = ALv;
+};
+
+constexpr int even_up(int v) { return v + (v & 1); }
+constexpr int odd_up(int v) { return v | 1; }
+constexpr int max_of(int a, int b) { return a > b ? a : b; }
+
+// LDS of the 3D eigenbasis form (T words; "pairs" are two words moved by one access).  Stage A fills
+// region A, stage B region B, stages C and D the transpose buffers W6 and W7.  Each buffer has the
+// loop index of its reading stage outermost.
+template <int K, typename SH>
+struct EigLds3 {
+  static constexpr int PPW = SH::PPW, n = 2 * K + 1, m = 2 * K - 1, mm = m * m, NF = 2 * PPW;
+  static constexpr int SI1 = pad32(PPW * mm, m);     // BT [i1][q][a2][i0]
+  static constexpr int SF0 = odd_up(NF * m);         // x0 faces, pairs [j1][q][end][a2]
+  static constexpr int SF1 = odd_up(4 * PPW * m);    // x1 / x2 faces, pairs [i0][face][end][q][a2 or a1]
+  static constexpr int offF0 = even_up(m * SI1), offF1 = offF0 + 2 * n * SF0;
+  static constexpr int RA = offF1 + 2 * m * SF1;
+  static constexpr int SI0 = pad32(PPW * mm, 1);     // W5 [i0][q][a2][a1]
+  static constexpr int oP0 = even_up(m * SI0);       // pairs [q][end][a2][a1]
+  static constexpr int oP1 = oP0 + 2 * NF * mm;      // pairs [a0][face][parity][q][a2 or a1]
+  static constexpr int RB = oP1 + 2 * m * SF1;
+  static constexpr int SA1 = pad32(PPW * mm, 1);     // W6 [a1][q][a2][i0]
+  static constexpr int SA2 = pad32(PPW * mm, m);     // W7 [a2][i1][q][i0]
+  static constexpr int W6 = even_up(m * SA1), W7 = even_up(m * SA2);
+  static constexpr int A = max_of(RA, W6), B = max_of(RB, W7);
+  static constexpr int offB = SH::AL ? 0 : A;
+  static constexpr int offW6 = 0, offW7 = SH::AL ? W6 : A;
+  static constexpr int offC = SH::AL ? max_of(max_of(RA, RB), W6 + W7) : A + B;  // the patches' constants
+  static constexpr int total = offC + PPW;
+};
+
+// 3D eigenbasis pass.  Stages (tasks, the axis transformed):
+//   A  b lines (i1, q, i0)       x2: S^T b                                  -> BT
+//      rim columns of the patch closures in the (x0, x1) plane
+//                                x2: (Mt, At) (x - c)                       -> x0 / x1 faces
+//      x2-face lines (end, q, i0) x1: W (x - c) and its lambda multiple     -> x2 faces
+//   B  b lines (q, a2, i0)       x1: S^T                                    -> W5
+//      x0-face lines (q, end, a2) x1: P, Q                                  -> PQ0
+//      x1- and x2-face lines (face, parity, q, a2 or a1)  x0: P, Q          -> PQ1
+//   C  lines (q, a2, a1)         x0: S^T b, minus the face terms, 1/(lam2 + lam1 + lam0), S -> W6
+//   D  lines (q, a2, i0)         x1: S                                      -> W7
+//   E  lines (i1, q, i0)         x2: S, plus c, straight to global
+// The lists of stages A and B are cut into whole waves per kind of task, so no wave mixes two kinds.
+// POISON: a non-finite old interior value makes the patch's result non-finite, as the residual form
+// does (x^I enters through one multiply-add by zero per node); without it x^I is never read.
+template <int K, typename T, bool POISON, typename SH>
+__device__ __forceinline__ void colour_pass_eig3(T* __restrict__ smem, const T* __restrict__ b, T* __restrict__ x,
+                                                 long long n1d, int p0, int p1, int p2, int cnt0, int cnt1,
+                                                 int groups0, T sol_scale, unsigned blk) {
+  constexpr int n = 2 * K + 1, m = 2 * K - 1, mm = m * m;
+  constexpr int PPW = SH::PPW, NT = SH::NT, NW = NT / 64;
+  static_assert(NT % 64 == 0, "whole waves");
+  using PT = gen::PatchTables<T, K>;
+  using L = EigLds3<K, SH>;
+  using T2 = typename Pair<T>::type;
+  constexpr int NF = 2 * PPW;  // x0 faces
+
+  const ColourBlock cb = colour_block<3, K, PPW>(blk, p0, p1, p2, cnt0, cnt1, groups0);
+  const int P = cb.count;
+  const long long s0 = cb.s0, s1 = cb.s1, s2 = cb.s2;
+  const long long n1d2 = n1d * n1d;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int seg = 2 * K * P + 1;  // valid closure columns along x0
+  const int ld1 = (int)n1d;
+  // windows at the closure corner of the first patch
+  const unsigned span = (unsigned)(2 * K * (n1d2 + n1d) + seg) * (unsigned)sizeof(T);  // below 4 GiB (launcher)
+  const Window<T> xw(x + (s2 * n1d2 + s1 * n1d + s0), span), bw(b + (s2 * n1d2 + s1 * n1d + s0), span);
+  // byte offsets of the closure's planes and of its rows, as scalars: derived again inside divergent
+  // branches they would become per-lane values and every access a loop over the lanes
+  unsigned pl[n], rw[m];
+#pragma unroll
+  for (int j = 0; j < n; ++j) pl[j] = __builtin_amdgcn_readfirstlane((unsigned)(j * n1d2) * (unsigned)sizeof(T));
+#pragma unroll
+  for (int i = 0; i < m; ++i) rw[i] = __builtin_amdgcn_readfirstlane((unsigned)(i * n1d) * (unsigned)sizeof(T));
+  const bool lo0 = s0 == 0, hi0 = s0 + seg - 1 == n1d - 1;
+  const bool lo1 = s1 == 0, hi1 = s1 + n - 1 == n1d - 1;
+  const bool lo2 = s2 == 0, hi2 = s2 + n - 1 == n1d - 1;
+
+  // the constant of patch q: the mean of its two extreme closure corners (a Dirichlet corner is 0)
+  auto patch_constant = [&](int q) -> T {
+    const unsigned lo = (unsigned)(2 * K * q) * (unsigned)sizeof(T);
+    const unsigned hi = pl[2 * K] + (unsigned)(2 * K * (ld1 + q + 1)) * (unsigned)sizeof(T);
+    const T u = xw.load(0, (q == 0 && lo0) || lo1 || lo2 ? Window<T>::kOutside : lo);
+    const T v = xw.load(0, (q == P - 1 && hi0) || hi1 || hi2 ? Window<T>::kOutside : hi);
+    return T(0.5) * (u + v);
+  };
+
+  // ---- A: the b lines' loads first, then the face lines, then the b transforms
+  constexpr int NB = PPW * mm;                    // b lines
+  constexpr int NR = 2 * PPW * (n + m);           // rim columns
+  constexpr int NX = 2 * PPW * m;                 // x2-face lines
+  constexpr int WB = (NB + 63) / 64, WR = (NR + 63) / 64, WX = (NX + 63) / 64;
+  constexpr int RNDA = (WB + WR + WX + NW - 1) / NW;
+  constexpr int RNB = (WB + NW - 1) / NW;         // rounds of the waves that hold b lines
+  {
+    T v[RNB][m], xp[RNB][m];
+    auto b_line = [&](int u, int& i1, int& q, int& i0) -> bool {
+      const int t = u * 64 + lane;
+      i1 = div_small<PPW * m>(t);
+      const int r = t - i1 * (PPW * m);
+      q = div_small<m>(r);
+      i0 = r - q * m;
+      return t < NB && q < P;
+    };
+#pragma unroll
+    for (int rr = 0; rr < RNB; ++rr) {
+      const int u = rr * NW + wave;
+      int i1, q, i0;
+      if (u < WB && b_line(u, i1, q, i0)) {
+        const unsigned off = (unsigned)((1 + i1) * ld1 + 2 * K * q + 1 + i0) * (unsigned)sizeof(T);
+#pragma unroll
+        for (int i = 0; i < m; ++i) v[rr][i] = bw.load(pl[1 + i], off);
+        if constexpr (POISON) {
+#pragma unroll
+          for (int i = 0; i < m; ++i) xp[rr][i] = xw.load(pl[1 + i], off);
+        }
+      }
+    }
+    // face lines of wave-task u
+    auto face_line = [&](int u) {
+      if (u < WB + WR) {
+        const int t = (u - WB) * 64 + lane;
+        // the columns j1 = 0 and n - 1 of every patch, then its side columns (c = 0 and n - 1)
+        int j1, q, c;
+        if (t < 2 * PPW * n) {
+          const int r = t < PPW * n ? t : t - PPW * n;
+          j1 = t < PPW * n ? 0 : n - 1;
+          q = div_small<n>(r);
+          c = r - q * n;
+        } else {
+          const int g = t - 2 * PPW * n, jj = div_small<NF>(g), r = g - jj * NF;
+          j1 = 1 + jj;
+          q = r >> 1;
+          c = (r & 1) * (n - 1);
+        }
+        if (t < NR && q < P) {
+          const int end = c == 0 ? 0 : 1, col = 2 * K * q + c;
+          const bool f0 = c == 0 || c == n - 1;  // x0 face, else x1 face
+          // Dirichlet nodes count as 0 (the boundary entries of x are not read as values)
+          const bool z = (col == 0 && lo0) || (col == seg - 1 && hi0) || (j1 == 0 && lo1) || (j1 == n - 1 && hi1);
+          const unsigned off = z ? Window<T>::kOutside : (unsigned)(__mul24(j1, ld1) + col) * (unsigned)sizeof(T);
+          T w[n], r[m], Ee, Eo;
+#pragma unroll
+          for (int j = 0; j < n; ++j) w[j] = xw.load(pl[j], off);
+          const T cq = patch_constant(q);
+          if (lo2) w[0] = T(0);
+          if (hi2) w[n - 1] = T(0);
+#pragma unroll
+          for (int j = 0; j < n; ++j) w[j] -= cq;
+          if (j1 == 0 && c == 0) smem[L::offC + q] = cq;
+          apply_mt<T, K>(w, r, Ee, Eo);
+          T2* F = reinterpret_cast<T2*>(smem) +
+                  lds_base(f0 ? L::offF0 / 2 + j1 * L::SF0 + (2 * q + end) * m
+                              : L::offF1 / 2 + (c - 1) * L::SF1 + ((j1 == 0 ? 0 : PPW) + q) * m);
+#pragma unroll
+          for (int a = 0; a < m; ++a) F[a] = T2{r[a], fma(PT::be[a], a < K ? +Ee : +Eo, PT::lam[a] * r[a])};
+        }
+      } else {
+        const int t = (u - WB - WR) * 64 + lane;
+        const int e = div_small<PPW * m>(t), g = t - e * (PPW * m), q = div_small<m>(g), i0 = g - q * m;
+        if (t < NX && q < P) {
+          const unsigned off = (e == 0 ? lo2 : hi2)
+                                   ? Window<T>::kOutside
+                                   : (e == 0 ? 0u : pl[2 * K]) + (unsigned)(ld1 + 2 * K * q + 1 + i0) * (unsigned)sizeof(T);
+          T w[m], r[m];
+#pragma unroll
+          for (int i = 0; i < m; ++i) w[i] = xw.load(rw[i], off);
+          const T cq = patch_constant(q);
+#pragma unroll
+          for (int i = 0; i < m; ++i) w[i] -= cq;
+          apply_w<T, K>(w, r);
+          T2* F = reinterpret_cast<T2*>(smem) + lds_base(L::offF1 / 2 + i0 * L::SF1 + ((2 + e) * PPW + q) * m);
+#pragma unroll
+          for (int a = 0; a < m; ++a) F[a] = T2{r[a], PT::lam[a] * r[a]};
+        }
+      }
+    };
+#pragma unroll
+    for (int rr = WB / NW; rr < RNDA; ++rr) {
+      const int u = rr * NW + wave;
+      if (u >= WB && u < WB + WR + WX) face_line(u);
+    }
+#pragma unroll
+    for (int rr = 0; rr < RNB; ++rr) {
+      const int u = rr * NW + wave;
+      int i1, q, i0;
+      if (u < WB && b_line(u, i1, q, i0)) {
+        T r[m];
+        if constexpr (POISON) {
+#pragma unroll
+          for (int i = 0; i < m; ++i) v[rr][0] = fma(T(0), xp[rr][i], v[rr][0]);
+        }
+        apply_st<T, K>(v[rr], r);
+        const int ob = lds_base(i1 * L::SI1 + q * mm + i0);
+#pragma unroll
+        for (int a = 0; a < m; ++a) smem[ob + a * m] = r[a];
+      }
+    }
+  }
+  __syncthreads();
+  // ---- B
+  {
+    constexpr int NF0 = NF * m, NF1 = 4 * PPW * m;
+    constexpr int W0 = (NF0 + 63) / 64, W1 = (NF1 + 63) / 64, RNDB = (WB + W0 + W1 + NW - 1) / NW;
+    const T2* F0 = reinterpret_cast<const T2*>(smem + L::offF0);
+    const T2* F1 = reinterpret_cast<const T2*>(smem + L::offF1);
+    T* W5 = smem + L::offB;
+    T2* PQ0 = reinterpret_cast<T2*>(smem + L::offB + L::oP0);
+    T2* PQ1 = reinterpret_cast<T2*>(smem + L::offB + L::oP1);
+    T rb[RNB][m], r0[RNDB][m], r1[RNDB][m];
+    // patches past the last one: whatever the buffers hold, never stored to global
+    auto b_work = [&](int u, T (&a0)[m]) {
+      const int t = u * 64 + lane;
+      if (u < WB && t < NB) {
+        T in[m];
+#pragma unroll
+        for (int i = 0; i < m; ++i) in[i] = smem[i * L::SI1 + t];
+        apply_st<T, K>(in, a0);
+      }
+    };
+    auto b_put = [&](int u, const T (&a0)[m]) {
+      const int t = u * 64 + lane;
+      if (u < WB && t < NB) {
+        const int r = div_small<m>(t), i0 = t - r * m;  // r = q * m + a2
+        const int ob = lds_base(i0 * L::SI0 + r * m);
+#pragma unroll
+        for (int a = 0; a < m; ++a) W5[ob + a] = a0[a];
+      }
+    };
+    // face task u of the wave: P in a0, Q in a1
+    auto work = [&](int u, T (&a0)[m], T (&a1)[m]) {
+      if (u < WB) return;
+      if (u < WB + W0) {
+        const int t = (u - WB) * 64 + lane;
+        if (t < NF0) {
+          T mv[n], av[n], Ee, Eo, Fe, Fo, q[m];
+#pragma unroll
+          for (int j = 0; j < n; ++j) {
+            const T2 w = F0[j * L::SF0 + t];
+            mv[j] = w.x;
+            av[j] = w.y;
+          }
+          apply_mt<T, K>(mv, a0, Ee, Eo);
+          apply_mt<T, K>(av, q, Fe, Fo);
+#pragma unroll
+          for (int a = 0; a < m; ++a) a1[a] = fma(PT::be[a], a < K ? +Ee : +Eo, fma(PT::lam[a], a0[a], q[a]));
+        }
+      } else if (u < WB + W0 + W1) {
+        const int t = (u - WB - W0) * 64 + lane;
+        if (t < NF1) {
+          // (face, parity, q, a): the sum or difference of the face's two ends
+          const int g = div_small<PPW * m>(t), par = g & 1, base = (g - par) * (PPW * m) + (t - g * (PPW * m));
+          const T sg = par ? T(-1) : T(1);
+          T mv[m], av[m], q[m];
+#pragma unroll
+          for (int i = 0; i < m; ++i) {
+            const T2 lf = F1[i * L::SF1 + base], rt = F1[i * L::SF1 + base + PPW * m];
+            mv[i] = fma(sg, rt.x, lf.x);
+            av[i] = fma(sg, rt.y, lf.y);
+          }
+          apply_w<T, K>(mv, a0);
+          apply_w<T, K>(av, q);
+#pragma unroll
+          for (int a = 0; a < m; ++a) a1[a] = fma(PT::lam[a], a0[a], q[a]);
+        }
+      }
+    };
+    auto put = [&](int u, const T (&a0)[m], const T (&a1)[m]) {
+      if (u < WB) return;
+      if (u < WB + W0) {
+        const int t = (u - WB) * 64 + lane;
+        if (t < NF0) {
+          T2* d = PQ0 + lds_base(t * m);
+#pragma unroll
+          for (int a = 0; a < m; ++a) d[a] = T2{a0[a], a1[a]};
+        }
+      } else if (u < WB + W0 + W1) {
+        const int t = (u - WB - W0) * 64 + lane;
+        if (t < NF1) {
+          T2* d = PQ1 + lds_base(t);
+#pragma unroll
+          for (int a = 0; a < m; ++a) d[a * L::SF1] = T2{a0[a], a1[a]};
+        }
+      }
+    };
+    if constexpr (SH::AL) {
+#pragma unroll
+      for (int rr = 0; rr < RNB; ++rr) b_work(rr * NW + wave, rb[rr]);
+#pragma unroll
+      for (int rr = WB / NW; rr < RNDB; ++rr) work(rr * NW + wave, r0[rr], r1[rr]);
+      __syncthreads();
+#pragma unroll
+      for (int rr = 0; rr < RNB; ++rr) b_put(rr * NW + wave, rb[rr]);
+#pragma unroll
+      for (int rr = WB / NW; rr < RNDB; ++rr) put(rr * NW + wave, r0[rr], r1[rr]);
+    } else {
+#pragma unroll
+      for (int rr = 0; rr < RNB; ++rr) {
+        b_work(rr * NW + wave, rb[0]);
+        b_put(rr * NW + wave, rb[0]);
+      }
+#pragma unroll
+      for (int rr = WB / NW; rr < RNDB; ++rr) {
+        work(rr * NW + wave, r0[0], r1[0]);
+        put(rr * NW + wave, r0[0], r1[0]);
+      }
+    }
+  }
+  // ---- C
+  constexpr int RC = (NB + NT - 1) / NT;
+  {
+    const DevTables<T>& tb = tab_fresh<T>(K);
+    const T* W5 = smem + L::offB;
+    const T2* PQ0 = reinterpret_cast<const T2*>(smem + L::offB + L::oP0);
+    const T2* PQ1 = reinterpret_cast<const T2*>(smem + L::offB + L::oP1);
+    T* W6 = smem + L::offW6;
+    T w[RC][m], iv[RC][m], c1[RC][2], c2[RC][2];
+    // the lane's table entries, fetched before the barrier
+#pragma unroll
+    for (int rr = 0; rr < RC; ++rr) {
+      const int t = rr * NT + tid, r = t - div_small<mm>(t) * mm, a2 = div_small<m>(r), a1 = r - a2 * m;
+#pragma unroll
+      for (int a = 0; a < m; ++a) iv[rr][a] = tb.inv3[r * m + a];
+      c1[rr][0] = tb.al[a1];
+      c1[rr][1] = tb.mu[a1];
+      c2[rr][0] = tb.al[a2];
+      c2[rr][1] = tb.mu[a2];
+    }
+    __syncthreads();
+    auto put = [&](int t, const T (&v)[m]) {
+      const int q = div_small<mm>(t), r = t - q * mm, a2 = div_small<m>(r), a1 = r - a2 * m;
+      const int ob = lds_base(a1 * L::SA1 + q * mm + a2 * m);
+#pragma unroll
+      for (int i = 0; i < m; ++i) W6[ob + i] = v[i];
+    };
+#pragma unroll
+    for (int rr = 0; rr < RC; ++rr) {
+      const int t = rr * NT + tid;
+      const int q = div_small<mm>(t), r = t - q * mm, a2 = div_small<m>(r), a1 = r - a2 * m;
+      if (t < NB && q < P) {
+        T in[m], z[m];
+#pragma unroll
+        for (int i = 0; i < m; ++i) in[i] = W5[i * L::SI0 + t];
+        apply_st<T, K>(in, z);
+        const T2 f0 = PQ0[t + q * mm], f1 = PQ0[t + (q + 1) * mm];
+        const T pe = f0.x + f1.x, po = f0.x - f1.x, qe = f0.y + f1.y, qo = f0.y - f1.y;
+        const T2* F1 = PQ1 + lds_base((a1 < K ? 0 : PPW * m) + q * m + a2);
+        const T2* F2 = PQ1 + lds_base((a2 < K ? 2 : 3) * PPW * m + q * m + a1);
+#pragma unroll
+        for (int a = 0; a < m; ++a) {
+          const T2 u1 = F1[a * L::SF1], u2 = F2[a * L::SF1];
+          T g = PT::al[a] * (a < K ? +pe : +po);
+          g = fma(PT::mu[a], a < K ? +qe : +qo, g);
+          g = fma(c1[rr][0], u1.x, g);
+          g = fma(c1[rr][1], u1.y, g);
+          g = fma(c2[rr][0], u2.x, g);
+          g = fma(c2[rr][1], u2.y, g);
+          z[a] = fma(sol_scale, z[a], -g) * iv[rr][a];
+        }
+        apply_s<T, K>(z, w[rr]);
+        if constexpr (!SH::AL) put(t, w[rr]);
+      }
+    }
+    if constexpr (SH::AL) {
+      __syncthreads();
+#pragma unroll
+      for (int rr = 0; rr < RC; ++rr) {
+        const int t = rr * NT + tid;
+        if (t < NB && div_small<mm>(t) < P) put(t, w[rr]);
+      }
+    }
+  }
+  __syncthreads();
+  // ---- D
+  {
+    const T* W6 = smem + L::offW6;
+    T* W7 = smem + L::offW7;
+#pragma unroll
+    for (int rr = 0; rr < RC; ++rr) {
+      const int t = rr * NT + tid;
+      const int q = div_small<mm>(t), r = t - q * mm, a2 = div_small<m>(r), i0 = r - a2 * m;
+      if (t < NB && q < P) {
+        T in[m], w[m];
+#pragma unroll
+        for (int a = 0; a < m; ++a) in[a] = W6[a * L::SA1 + t];
+        apply_s<T, K>(in, w);
+        const int ob = lds_base(a2 * L::SA2 + q * m + i0);
+#pragma unroll
+        for (int i = 0; i < m; ++i) W7[ob + i * (PPW * m)] = w[i];
+      }
+    }
+  }
+  __syncthreads();
+  // ---- E
+  {
+    const T* W7 = smem + L::offW7;
+#pragma unroll
+    for (int rr = 0; rr < RC; ++rr) {
+      const int t = rr * NT + tid;
+      const int i1 = div_small<PPW * m>(t), r = t - i1 * (PPW * m), q = div_small<m>(r), i0 = r - q * m;
+      if (t < NB && q < P) {
+        T in[m], w[m];
+#pragma unroll
+        for (int a = 0; a < m; ++a) in[a] = W7[a * L::SA2 + t];
+        const T cq = smem[L::offC + q];
+        apply_s<T, K>(in, w);
+        const unsigned off = (unsigned)((1 + i1) * ld1 + 2 * K * q + 1 + i0) * (unsigned)sizeof(T);
+#pragma unroll
+        for (int i = 0; i < m; ++i) xw.store(pl[1 + i], off, w[i] + cq);
+      }
+    }
+  }
+}
+
+// LDS of the 2D eigenbasis form.
+template <int K, typename SH>
+struct EigLds2 {
+  static constexpr int PPW = SH::PPW, n = 2 * K + 1, m = 2 * K - 1, NF = 2 * PPW;
+  static constexpr int T0 = pad32(PPW * m, 1);        // W [i0][q][a1]
+  static constexpr int oP0 = even_up(m * T0);         // x0 faces, pairs (P, Q) [q][end][a1]
+  static constexpr int SP1 = odd_up(PPW);
+  static constexpr int oP1 = oP0 + 2 * NF * m;        // x1 faces, pairs (low end, high end) [a0][q]
+  static constexpr int RA = oP1 + 2 * m * SP1;
+  static constexpr int TA = pad32(PPW * m, 1);        // W2 [a1][q][i0]
+  static constexpr int offW2 = SH::AL ? 0 : RA;
+  static constexpr int offC = SH::AL ? max_of(RA, m * TA) : RA + m * TA;  // the patches' constants
+  static constexpr int total = offC + PPW;
+};
+
+// 2D eigenbasis pass.
+//   A  b lines (q, i0)            x1: S^T b                                 -> W
+//      face lines of x - c: x0 faces (q, end) along x1 (P = Mt F, Q = At F), x1 faces (end, q) along x0
+//      (W F)                                                              -> PQ0, P1
+//   B  lines (q, a1)              x0: S^T b, minus the face terms, 1/(lam1 + lam0), S -> W2
+//   C  lines (q, i0)              x1: S, plus c, straight to global
+template <int K, typename T, bool POISON, typename SH>
+__device__ __forceinline__ void colour_pass_eig2(T* __restrict__ smem, const T* __restrict__ b, T* __restrict__ x,
+                                                 long long n1d, int p0, int p1, int cnt0, int cnt1, int groups0,
+                                                 T sol_scale, unsigned blk) {
+  constexpr int n = 2 * K + 1, m = 2 * K - 1;
+  constexpr int PPW = SH::PPW, NT = SH::NT, NW = NT / 64;
+  static_assert(NT % 64 == 0, "whole waves");
+  using PT = gen::PatchTables<T, K>;
+  using L = EigLds2<K, SH>;
+  using T2 = typename Pair<T>::type;
+  constexpr int NF = 2 * PPW;  // x0 faces
+
+  const ColourBlock cb = colour_block<2, K, PPW>(blk, p0, p1, 0, cnt0, cnt1, groups0);
+  const int P = cb.count;
+  const long long s0 = cb.s0, s1 = cb.s1;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int seg = 2 * K * P + 1;
+  const int ld1 = (int)n1d;
+  // windows at the closure corner of the first patch
+  const unsigned span = (unsigned)(2 * K * n1d + seg) * (unsigned)sizeof(T);  // below 4 GiB (launcher)
+  const Window<T> xw(x + (s1 * n1d + s0), span), bw(b + (s1 * n1d + s0), span);
+  unsigned rw[m];  // byte offsets of the interior rows (scalars, as in the 3D form)
+#pragma unroll
+  for (int i = 0; i < m; ++i) rw[i] = __builtin_amdgcn_readfirstlane((unsigned)((1 + i) * n1d) * (unsigned)sizeof(T));
+  const bool lo0 = s0 == 0, hi0 = s0 + seg - 1 == n1d - 1;
+  const bool lo1 = s1 == 0, hi1 = s1 + n - 1 == n1d - 1;
+
+  constexpr int NB = PPW * m, NX = NF + 2 * PPW;  // b lines, face lines
+  constexpr int WB = (NB + 63) / 64, WX = (NX + 63) / 64, RNDA = (WB + WX + NW - 1) / NW;
+  T* W = smem;
+  T2* PQ0 = reinterpret_cast<T2*>(smem + L::oP0);
+  {
+    T v[RNDA][n], xp[RNDA][m], cq[RNDA];
+    // face line of wave-task u: x0 face (q, end e) or x1 face (end e, q)
+    auto face_line = [&](int u, bool& f0, int& q, int& e) -> bool {
+      const int t = (u - WB) * 64 + lane, g = t - NF;
+      f0 = t < NF;
+      e = f0 ? t & 1 : g >= PPW ? 1 : 0;
+      q = f0 ? t >> 1 : g - e * PPW;
+      return t < NX && q < P;
+    };
+#pragma unroll
+    for (int rr = 0; rr < RNDA; ++rr) {
+      const int u = rr * NW + wave;
+      if (u < WB) {
+        const int t = u * 64 + lane, q = div_small<m>(t), i0 = t - q * m;
+        if (t < NB && q < P) {
+          const unsigned off = (unsigned)(2 * K * q + 1 + i0) * (unsigned)sizeof(T);
+#pragma unroll
+          for (int i = 0; i < m; ++i) v[rr][i] = bw.load(rw[i], off);
+          if constexpr (POISON) {
+#pragma unroll
+            for (int i = 0; i < m; ++i) xp[rr][i] = xw.load(rw[i], off);
+          }
+        }
+      } else if (u < WB + WX) {
+        bool f0;
+        int q, e;
+        if (face_line(u, f0, q, e)) {
+          // node j of the line at off + j * stride
+          const unsigned off = (unsigned)(2 * K * (f0 ? q + e : q + e * ld1)) * (unsigned)sizeof(T);
+          const unsigned st = (unsigned)(f0 ? ld1 : 1) * (unsigned)sizeof(T);
+#pragma unroll
+          for (int j = 0; j < n; ++j) v[rr][j] = xw.load(0, off + (unsigned)j * st);
+          // the mean of the patch's two extreme closure corners (a Dirichlet corner is 0)
+          const unsigned hi = (unsigned)(2 * K * (ld1 + q + 1)) * (unsigned)sizeof(T);
+          cq[rr] = T(0.5) * (xw.load(0, (q == 0 && lo0) || lo1 ? Window<T>::kOutside : (unsigned)(2 * K * q) * (unsigned)sizeof(T)) +
+                             xw.load(0, (q == P - 1 && hi0) || hi1 ? Window<T>::kOutside : hi));
+        }
+      }
+    }
+#pragma unroll
+    for (int rr = 0; rr < RNDA; ++rr) {
+      const int u = rr * NW + wave;
+      if (u < WB) {
+        const int t = u * 64 + lane, q = div_small<m>(t), i0 = t - q * m;
+        if (t < NB && q < P) {
+          T w[m], s[m];
+#pragma unroll
+          for (int i = 0; i < m; ++i) {
+            w[i] = v[rr][i];
+            if constexpr (POISON) w[0] = fma(T(0), xp[rr][i], w[0]);
+          }
+          apply_st<T, K>(w, s);
+          const int ob = lds_base(i0 * L::T0 + q * m);
+#pragma unroll
+          for (int a = 0; a < m; ++a) W[ob + a] = s[a];
+        }
+      } else if (u < WB + WX) {
+        bool f0;
+        int q, e;
+        if (face_line(u, f0, q, e)) {
+          const bool z = f0 ? (q + e == 0 && lo0) || (q + e == P && hi0) : e ? hi1 : lo1;
+          T w[n], s[m], Ee, Eo;
+#pragma unroll
+          for (int j = 0; j < n; ++j) w[j] = z ? T(0) : v[rr][j];
+          if (lo1) w[0] = f0 ? T(0) : w[0];
+          if (hi1) w[n - 1] = f0 ? T(0) : w[n - 1];
+#pragma unroll
+          for (int j = 0; j < n; ++j) w[j] -= cq[rr];
+          if (!f0) w[0] = w[n - 1] = T(0);  // the corners belong to the x0 faces
+          if (f0 && e == 0) smem[L::offC + q] = cq[rr];
+          apply_mt<T, K>(w, s, Ee, Eo);
+          if (f0) {
+            T2* d = PQ0 + lds_base((2 * q + e) * m);
+#pragma unroll
+            for (int a = 0; a < m; ++a) d[a] = T2{s[a], fma(PT::be[a], a < K ? +Ee : +Eo, PT::lam[a] * s[a])};
+          } else {
+            T* d = smem + lds_base(L::oP1 + 2 * q + e);
+#pragma unroll
+            for (int a = 0; a < m; ++a) d[a * 2 * L::SP1] = s[a];
+          }
+        }
+      }
+    }
+  }
+  // ---- B
+  constexpr int RC = (NB + NT - 1) / NT;
+  {
+    const DevTables<T>& tb = tab_fresh<T>(K);
+    T* W2 = smem + L::offW2;
+    T w[RC][m], iv[RC][m], c1[RC][2];
+#pragma unroll
+    for (int rr = 0; rr < RC; ++rr) {
+      const int t = rr * NT + tid, a1 = t - div_small<m>(t) * m;
+#pragma unroll
+      for (int a = 0; a < m; ++a) iv[rr][a] = tb.inv2[a1 * m + a];
+      c1[rr][0] = tb.al[a1];
+      c1[rr][1] = tb.mu[a1];
+    }
+    __syncthreads();
+    auto put = [&](int t, const T (&v)[m]) {
+      const int q = div_small<m>(t), a1 = t - q * m;
+      const int ob = lds_base(a1 * L::TA + q * m);
+#pragma unroll
+      for (int i = 0; i < m; ++i) W2[ob + i] = v[i];
+    };
+#pragma unroll
+    for (int rr = 0; rr < RC; ++rr) {
+      const int t = rr * NT + tid, q = div_small<m>(t), a1 = t - q * m;
+      if (t < NB && q < P) {
+        T in[m], z[m];
+#pragma unroll
+        for (int i = 0; i < m; ++i) in[i] = W[i * L::T0 + t];
+        apply_st<T, K>(in, z);
+        const T2 f0 = PQ0[t + q * m], f1 = PQ0[t + (q + 1) * m];
+        const T pe = f0.x + f1.x, po = f0.x - f1.x, qe = f0.y + f1.y, qo = f0.y - f1.y;
+        const T sg = a1 < K ? T(1) : T(-1);
+        const T2* F1 = reinterpret_cast<const T2*>(smem + L::oP1) + lds_base(q);
+#pragma unroll
+        for (int a = 0; a < m; ++a) {
+          const T2 e = F1[a * L::SP1];
+          T g = PT::al[a] * (a < K ? +pe : +po);
+          g = fma(PT::mu[a], a < K ? +qe : +qo, g);
+          g = fma(fma(c1[rr][1], PT::lam[a], c1[rr][0]), fma(sg, e.y, e.x), g);
+          z[a] = fma(sol_scale, z[a], -g) * iv[rr][a];
+        }
+        apply_s<T, K>(z, w[rr]);
+        if constexpr (!SH::AL) put(t, w[rr]);
+      }
+    }
+    if constexpr (SH::AL) {
+      __syncthreads();
+#pragma unroll
+      for (int rr = 0; rr < RC; ++rr) {
+        const int t = rr * NT + tid;
+        if (t < NB && div_small<m>(t) < P) put(t, w[rr]);
+      }
+    }
+  }
+  __syncthreads();
+  // ---- C
+  {
+    const T* W2 = smem + L::offW2;
+#pragma unroll
+    for (int rr = 0; rr < RC; ++rr) {
+      const int t = rr * NT + tid, q = div_small<m>(t), i0 = t - q * m;
+      if (t < NB && q < P) {
+        T in[m], w[m];
+#pragma unroll
+        for (int a = 0; a < m; ++a) in[a] = W2[a * L::TA + t];
+        const T cq = smem[L::offC + q];
+        apply_s<T, K>(in, w);
+        const unsigned off = (unsigned)(2 * K * q + 1 + i0) * (unsigned)sizeof(T);
+#pragma unroll
+        for (int i = 0; i < m; ++i) xw.store(rw[i], off, w[i] + cq);
+      }
+    }
+  }
+}
+
+// Degree 1: a patch has one interior node, so the pass is a stencil (9 or 27 points) with one thread per
+// patch, PPW consecutive patches along x0 per one-wave workgroup, and neither LDS nor a barrier.  The
+// residual b - h^(d-2) Abar x is summed row by row from the 1D patch rows (Sec. 3.1.1), then
+// x^I += residual / (h^(d-2) diagonal); without OLD (Boundary mode) the old x^I counts as 0.
+template <int D, typename T, bool OLD, int PPW>
+__device__ __forceinline__ void colour_pass_q1(const T* __restrict__ b, T* __restrict__ x, long long n1d, int p0, int p1,
+                                               int p2, int cnt0, int cnt1, int groups0, T res_scale, T sol_scale,
+                                               unsigned blk) {
+  using PT = gen::PatchTables<T, 1>;
+  constexpr int n = 3, J2 = D == 3 ? n : 1;
+  const ColourBlock cb = colour_block<D, 1, PPW>(blk, p0, p1, p2, cnt0, cnt1, groups0);
+  const int q = threadIdx.x, seg = 2 * cb.count + 1;
+  const long long n1d2 = n1d * n1d, origin = (D == 3 ? cb.s2 * n1d2 : 0) + cb.s1 * n1d + cb.s0;
+  const unsigned span = (unsigned)((D == 3 ? 2 * n1d2 : 0) + 2 * n1d + seg) * (unsigned)sizeof(T);
+  const Window<T> xw(x + origin, span), bw(b + origin, span);
+  const bool lo0 = cb.s0 == 0, hi0 = cb.s0 + seg - 1 == n1d - 1;
+  const bool edge1[2] = {cb.s1 == 0, cb.s1 + 2 == n1d - 1};
+  const bool edge2[2] = {D == 3 && cb.s2 == 0, D == 3 && cb.s2 + 2 == n1d - 1};
+  if (q >= cb.count) return;
+  // the patch's columns 2q, 2q + 1, 2q + 2; Dirichlet columns read as 0
+  unsigned off[n];
+#pragma unroll
+  for (int c = 0; c < n; ++c) off[c] = (unsigned)(2 * q + c) * (unsigned)sizeof(T);
+  if (q == 0 && lo0) off[0] = Window<T>::kOutside;
+  if (q == cb.count - 1 && hi0) off[2] = Window<T>::kOutside;
+  const unsigned centre = (unsigned)((D == 3 ? n1d2 : 0) + n1d) * (unsigned)sizeof(T);
+  const T bv = bw.load(centre, off[1]);
+  T v[J2][n][n];
+#pragma unroll
+  for (int j2 = 0; j2 < J2; ++j2)
+#pragma unroll
+    for (int j1 = 0; j1 < n; ++j1) {
+      const unsigned row = (unsigned)((D == 3 ? j2 * n1d2 : 0) + j1 * n1d) * (unsigned)sizeof(T);
+      const bool dirichlet = (j1 == 0 && edge1[0]) || (j1 == 2 && edge1[1]) ||
+                             (D == 3 && ((j2 == 0 && edge2[0]) || (j2 == 2 && edge2[1])));
+#pragma unroll
+      for (int c = 0; c < n; ++c) v[j2][j1][c] = dirichlet ? T(0) : xw.load(row, off[c]);
+    }
+  constexpr int jc = D == 3 ? 1 : 0;
+  const T old = v[jc][1][1];
+  if (!OLD) v[jc][1][1] = T(0);
+  T sum = T(0);
+#pragma unroll
+  for (int j2 = 0; j2 < J2; ++j2) {
+    T u = T(0), w = T(0);
+#pragma unroll
+    for (int j1 = 0; j1 < n; ++j1) {
+      T pm = T(0), pa = T(0);
+#pragma unroll
+      for (int c = 0; c < n; ++c) {
+        pm = fma(PT::Mc[c], v[j2][j1][c], pm);
+        pa = fma(PT::Ac[c], v[j2][j1][c], pa);
+      }
+      u = fma(PT::Mc[j1], pm, u);
+      w = fma(PT::Ac[j1], pm, fma(PT::Mc[j1], pa, w));
+    }
+    sum = D == 3 ? fma(PT::Ac[j2], u, fma(PT::Mc[j2], w, sum)) : w;
+  }
+  constexpr T inv = (T)(1.0 / (D * 2.0 * (D == 3 ? 4.0 / 9.0 : 2.0 / 3.0)));  // patch matrix of h = 1: d A M^(d-1)
+  const T r = fma(-res_scale, sum, bv) * inv;
+  xw.store(centre, off[1], OLD ? fma(sol_scale, r, old) : sol_scale * r);
+}
+
+// Launch shapes of the multiplicative and Boundary passes per (dim, degree, precision): Large, and the
+// Small one that a launch takes when Large would give fewer than kEigWaves waves.  Both columns are
+// the fastest of 5-20 (patches, threads, layout) per row over the levels they serve; patches per
+// workgroup that divide the power-of-two rows leave no slot idle.
+// Measured, back-to-back passes of a step, us, the residual form's in brackets, FP32 / FP64: 3D degree 3, 64^3
+// cells 20.2 (23.2) / 29.9 (32.3); degree 4, 64^3 38.5 (46.5) / 73.4 (83.7); degree 5, 32^3 13.3 (16.9) / 24.1
+// (27.7); degree 6, 32^3 21.7 (25.9) / 38.8 (47.7); degree 7, 32^3 33.7 (40.9) / 62.3 (78.1); 2D 512^2 degree 5
+// 16.3 (17.9) / 27.3 (31.5), degree 6 22.2 (24.4) / 38.7 (47.9), degree 7 27.9 (31.4) / 52.1 (65.5).
+// 3D degree 4 FP32 issues 14.9-16.3 M vector instructions a pass (18.8 M), 77% of its cycles, and its LDS pipe is
+// busy 80% of them; the FP64 passes run at 4.6-5.1 TB/s of closure-once traffic.
+template <int PPWv>
+struct Q1Shape {
+  static constexpr int PPW = PPWv, NT = PPWv;
+};
+template <int D, int K, typename T>
+struct EigShapes;
+template <typename T> struct EigShapes<3, 1, T> { using Large = Q1Shape<64>; using Small = Large; };
+template <typename T> struct EigShapes<3, 2, T> { using Large = EigShape<16, 256, true>; using Small = EigShape<4, 192, false>; };
+template <typename T> struct EigShapes<3, 3, T> { using Large = EigShape<5, 192, true>; using Small = EigShape<2, 192, false>; };
+template <> struct EigShapes<3, 4, float> { using Large = EigShape<4, 256, true>; using Small = EigShape<1, 192, false>; };
+template <> struct EigShapes<3, 4, double> { using Large = EigShape<2, 128, true>; using Small = EigShape<1, 192, false>; };
+template <typename T> struct EigShapes<3, 5, T> { using Large = EigShape<3, 256, true>; using Small = EigShape<1, 256, false>; };
+template <typename T> struct EigShapes<3, 6, T> { using Large = EigShape<2, 256, true>; using Small = EigShape<1, 256, false>; };
+template <> struct EigShapes<3, 7, float> { using Large = EigShape<1, 320, true>; using Small = EigShape<1, 320, false>; };
+template <> struct EigShapes<3, 7, double> { using Large = EigShape<1, 192, true>; using Small = EigShape<1, 320, false>; };
+template <typename T> struct EigShapes<2, 1, T> { using Large = Q1Shape<64>; using Small = Large; };
+template <typename T> struct EigShapes<2, 2, T> { using Large = EigShape<42, 192, false>; using Small = EigShape<8, 128, false>; };
+template <typename T> struct EigShapes<2, 3, T> { using Large = EigShape<32, 256, false>; using Small = EigShape<8, 128, false>; };
+template <typename T> struct EigShapes<2, 4, T> { using Large = EigShape<8, 128, false>; using Small = EigShape<4, 128, false>; };
+template <typename T> struct EigShapes<2, 5, T> { using Large = EigShape<14, 192, false>; using Small = EigShape<4, 128, false>; };
+template <typename T> struct EigShapes<2, 6, T> { using Large = EigShape<11, 192, false>; using Small = EigShape<4, 128, false>; };
+template <typename T> struct EigShapes<2, 7, T> { using Large = EigShape<9, 192, true>; using Small = EigShape<4, 128, false>; };
+constexpr long long kEigWaves = 1100;
+// 3D degree 7 in FP32 takes three patches per workgroup where the iterate and the right-hand side do not fit the
+// 256 MB last-level cache together: longer row segments for HBM (64^3 cells: 254 us a pass against 274; on 32^3,
+// which fits, 36.1 against 30.7).
+constexpr long long kLastLevelCache = 256LL << 20;
+template <int D, int K, typename T>
+struct FarShape {
+  using type = void;
+};
+template <> struct FarShape<3, 7, float> { using type = EigShape<3, 512, true>; };
+// ------------------------------------------------------------------ residual form
 
 // LDS of the 3D multiplicative pass below (T words).  Buffer A holds PM, PA [i2][j1][c], later the
 // results of stages C and E; buffer B holds U, V, later those of D and F.  Every transpose buffer
@@ -268,8 +1064,9 @@ struct Mult3Lds {
   static constexpr int B = max3(2 * n * SU, m * SW2, m * SW4);
   // Aliased layout: PM/PA, U/V and the C->D buffer all start at word 0 (stages B and C compute
   // every line, the workgroup synchronises, then they write over their inputs); the D->E and F->G
-  // buffers follow the larger of C->D and E->F, which starts at 0 again.
-  static constexpr bool AL = ((VPS_MULT3_ALIAS_MASK) >> K) & 1;
+  // buffers follow the larger of C->D and E->F, which starts at 0 again.  Measured 11-45% faster for
+  // degrees 2-7 (occupancy: 3D Q4 goes from 33 to 17 KB of LDS, from 8 to 18 waves per compute unit).
+  static constexpr bool AL = K >= 2;
   static constexpr int X1 = m * SW > m * SW3 ? m * SW : m * SW3;
   static constexpr int ALT = max3(2 * PM, 2 * n * SU, X1 + (m * SW2 > m * SW4 ? m * SW2 : m * SW4));
   static constexpr int total = AL ? ALT : A + B;
@@ -581,53 +1378,39 @@ __device__ __forceinline__ void colour_pass_mult3(T* __restrict__ smem, const T*
   }
 }
 
-// Wide shape of the 3D Q4 FP32 colour pass (multiplicative, Boundary, and the first colour from
-// zero): five patches per workgroup on 256 threads.  Its 49-line stages fill 245 of 256 lanes,
+// Wide shape of the 3D Q4 FP32 colour pass (residual form, and the first colour from zero): five patches per workgroup on 256 threads.  Its 49-line stages fill 245 of 256 lanes,
 // against 98 of 128 for the two-patch default, which cuts the vector instructions per patch by
 // about a fifth.  A row of patches along x0 that is not a multiple of five leaves a partial
 // workgroup, so launches take it only on long rows (at most kWideIdle idle patch slots per row, as a
 // fraction of the row).
-#ifndef VPS_Q4_3D_WIDE
-#define VPS_Q4_3D_WIDE 1
-#endif
 constexpr int kWidePPW = 5, kWideNT = 256;
 constexpr double kWideIdle = 0.15;
 template <int D, int K, typename T, int MODE>
 struct HasWideForm {
   static constexpr bool value = D == 3 && K == 4 && sizeof(T) == 4 &&
-                                (MODE == kModeMultiplicative || MODE == kModeZero || MODE == kModeBoundary) &&
-                                VPS_Q4_3D_WIDE;
+                                (MODE == kModeResidual || MODE == kModeZero);
 };
 template <int D, int K, typename T, int MODE, int PPW>
 struct IsWide {
   static constexpr bool value = HasWideForm<D, K, T, MODE>::value && PPW == kWidePPW;
 };
 
-// Degrees (bit K) whose default 3D multiplicative shape also takes the paired layout (the wide
+// Degrees whose default 3D residual-form shape also takes the paired layout (the wide
 // shape always does): 1-2.5% faster for degrees 5-7 (3D Q7: 30.8 -> 24.8 KB), equal for 3 and 4.
-#ifndef VPS_3D_PAIR_MASK
-#define VPS_3D_PAIR_MASK 0xE0
-#endif
 template <int D, int K, typename T, int MODE, int PPW>
 struct LinesPair {
   static constexpr bool value =
       IsWide<D, K, T, MODE, PPW>::value ||
-      (D == 3 && MODE == kModeMultiplicative && (((VPS_3D_PAIR_MASK) >> K) & 1) && PPW == SmootherShape<3, K>::PPW);
+      (D == 3 && MODE == kModeResidual && K >= 5 && PPW == SmootherShape<3, K>::PPW);
 };
 
-// Degrees (bit K) whose default 2D multiplicative shape takes the aliased LDS layout.
-#ifndef VPS_2D_ALIAS_MASK
-#define VPS_2D_ALIAS_MASK 0xFE
-#endif
-
-// The aliased LDS layout serves the default shape of the multiplicative pass where the shape asks
-// for it, and the wide shape.
+// The aliased LDS layout serves the default shape of the residual form where the shape asks for it (2D:
+// always), and the wide shape.
 template <int D, int K, typename T, int MODE, int PPW>
 struct LinesAlias {
   static constexpr bool value =
-      (D == 3 && MODE == kModeMultiplicative && SmootherShape<3, K>::ALIAS && PPW == SmootherShape<3, K>::PPW) ||
-      (D == 2 && MODE == kModeMultiplicative && (((VPS_2D_ALIAS_MASK) >> K) & 1) &&
-       PPW == SmootherShape<2, K>::PPW) ||
+      (D == 3 && MODE == kModeResidual && SmootherShape<3, K>::ALIAS && PPW == SmootherShape<3, K>::PPW) ||
+      (D == 2 && MODE == kModeResidual && PPW == SmootherShape<2, K>::PPW) ||
       IsWide<D, K, T, MODE, PPW>::value;
 };
 
@@ -641,7 +1424,7 @@ __device__ __forceinline__ void colour_pass_lines(T* __restrict__ smem, const T*
   constexpr int NT = IsWide<D, K, T, MODE, PPW>::value ? kWideNT : SmootherShape<D, K>::NT;
   // ZERO: the additive pass on x = 0 that also writes the zeros of the rest of its closures
   constexpr bool ZERO = MODE == kModeZero;
-  constexpr bool ADD = MODE == kModeAdditive || ZERO, BND = MODE == kModeBoundary;
+  constexpr bool ADD = MODE == kModeAdditive || ZERO;
   // patch matrices and eigenvectors as compile-time constants (instruction literals / SGPR moves)
   using PT = gen::PatchTables<T, K>;
   using L = SmootherLds<D, K, T, ADD, PPW, LinesAlias<D, K, T, MODE, PPW>::value, LinesPair<D, K, T, MODE, PPW>::value>;
@@ -745,8 +1528,6 @@ __device__ __forceinline__ void colour_pass_lines(T* __restrict__ smem, const T*
   // ---- closure segment -> LDS X [j2][j1][c].  Work item = (column c, row j1 in 3D); the
   // slowest axis is walked unrolled.  Every closure node lies inside the grid: loads are
   // unconditional and Dirichlet nodes are replaced by 0 (boundary entries of x are ignored).
-  // Boundary mode also replaces patch-interior nodes by 0 and does not load them: a column
-  // strictly inside a patch along x0 (and x1 in 3D) needs only its two end nodes.
   if constexpr (!ADD) {
     T* X = smem + (D == 3 ? L::offX : L::offX2);
     constexpr int NW = D == 3 ? RS * n : RS;
@@ -760,17 +1541,9 @@ __device__ __forceinline__ void colour_pass_lines(T* __restrict__ smem, const T*
       if constexpr (D == 3) bad = bad || (j1 == 0 && lo1) || (j1 == n - 1 && hi1);
       const unsigned base = ((D == 3 ? j1 * ld1 : 0) + cl) * (unsigned)sizeof(T);
       const int sstride = D == 3 ? ld2 : ld1;
-      // column strictly inside a patch (Boundary mode: its nodes 1..n-2 are patch-interior)
-      const bool inner = BND && cl % (2 * K) != 0 && (D == 2 || (j1 > 0 && j1 < n - 1));
       T v[n];
 #pragma unroll
-      for (int j = 0; j < n; ++j) {
-        if (BND && j > 0 && j < n - 1) {
-          v[j] = inner ? T(0) : ld_lane(xo + j * sstride, base);
-        } else {
-          v[j] = ld_lane(xo + j * sstride, base);
-        }
-      }
+      for (int j = 0; j < n; ++j) v[j] = ld_lane(xo + j * sstride, base);
       const bool lo = D == 3 ? lo2 : lo1, hi = D == 3 ? hi2 : hi1;
       if (c < seg) {
 #pragma unroll
@@ -781,13 +1554,11 @@ __device__ __forceinline__ void colour_pass_lines(T* __restrict__ smem, const T*
       }
     }
     __syncthreads();
-    if constexpr (!BND) {
-      // old x^I of this thread's lines: patch-interior nodes are never Dirichlet nodes
+    // old x^I of this thread's lines: patch-interior nodes are never Dirichlet nodes
 #pragma unroll
-      for (int rr = 0; rr < RB; ++rr) {
+    for (int rr = 0; rr < RB; ++rr) {
 #pragma unroll
-        for (int i = 0; i < m; ++i) xpre[rr][i] = X[xoff[rr] + i * (D == 3 ? n * RS : RS)];
-      }
+      for (int i = 0; i < m; ++i) xpre[rr][i] = X[xoff[rr] + i * (D == 3 ? n * RS : RS)];
     }
   }
 
@@ -801,111 +1572,7 @@ __device__ __forceinline__ void colour_pass_lines(T* __restrict__ smem, const T*
       T2* PP = reinterpret_cast<T2*>(smem + L::offP);  // paired layout: [j1][q][j2][i0]{M, A}
       constexpr int SJP2 = L::SJP / 2;                  // pair stride
       // ---- contract x0 with Mc and Ac: lines (q, j2, j1), j1 fastest
-      if constexpr (BND) {
-        // Boundary form: the closure is zero on patch-interior nodes, so an x0 line with j2 and j1
-        // both interior holds only its two end values.  The 4(n-1) face lines of each patch come
-        // first and take the full contraction, the m^2 interior lines a two-term one.
-        constexpr int NF = 4 * (n - 1);
-        // face tasks padded to whole waves, so that no wave mixes the two kinds of line
-        constexpr int FP = (PPW * NF + 63) / 64 * 64, NTASK = FP + PPW * mm;
-        // task -> line (q, j2, j1); false for padding and for patches past the workgroup's last
-        auto line_of = [&](int task, int& q, int& j2, int& j1) -> bool {
-          if (task >= NTASK || (task >= PPW * NF && task < FP)) return false;
-          if (task < FP) {
-            q = task / NF;
-            const int f = task - q * NF;
-            if (f < n) {
-              j2 = 0;
-              j1 = f;
-            } else if (f < 2 * n) {
-              j2 = n - 1;
-              j1 = f - n;
-            } else {
-              j2 = 1 + (f - 2 * n) / 2;
-              j1 = (f & 1) ? n - 1 : 0;  // f - 2n and f have the same parity (2n even)
-            }
-          } else {
-            const int t = task - FP;
-            q = t / mm;
-            const int c = t - q * mm;
-            j2 = 1 + c / m;
-            j1 = 1 + (c - (c / m) * m);
-          }
-          return q < P;
-        };
-        // M and A rows of one line into sm, sa
-        auto contract = [&](bool face, int row, T* sm, T* sa) {
-          if (face) {
-            T in[n];
-#pragma unroll
-            for (int j = 0; j < n; ++j) in[j] = X[row + j];
-#pragma unroll
-            for (int i = 0; i < m; ++i) {
-              T am = T(0), aa = T(0);
-#pragma unroll
-              for (int j = 0; j < n; ++j) {
-                am = fma_tab(PT::Mc[i * n + j], in[j], am);
-                aa = fma_tab(PT::Ac[i * n + j], in[j], aa);
-              }
-              sm[i] = am;
-              sa[i] = aa;
-            }
-          } else {
-            const T e0 = X[row], e1 = X[row + n - 1];
-#pragma unroll
-            for (int i = 0; i < m; ++i) {
-              sm[i] = fma_tab(PT::Mc[i * n], e0, fma_tab(PT::Mc[i * n + n - 1], e1, T(0)));
-              sa[i] = fma_tab(PT::Ac[i * n], e0, fma_tab(PT::Ac[i * n + n - 1], e1, T(0)));
-            }
-          }
-        };
-        if constexpr (L::AL) {
-          // aliased: every line is read and contracted, then PM/PA overwrite X
-          constexpr int RA = (NTASK + NT - 1) / NT;
-          T om[RA][m], oa[RA][m];
-#pragma unroll
-          for (int rr = 0; rr < RA; ++rr) {
-            const int task = rr * NT + tid;
-            int q, j2, j1;
-            if (line_of(task, q, j2, j1))
-              contract(task < FP, lds_base((j2 * n + j1) * RS + 2 * K * q), om[rr], oa[rr]);
-          }
-          __syncthreads();
-#pragma unroll
-          for (int rr = 0; rr < RA; ++rr) {
-            const int task = rr * NT + tid;
-            int q, j2, j1;
-            if (line_of(task, q, j2, j1)) {
-              if constexpr (L::PR) {
-                const int o = lds_base(j1 * SJP2 + (q * n + j2) * m);
-#pragma unroll
-                for (int i = 0; i < m; ++i) PP[o + i] = T2{om[rr][i], oa[rr][i]};
-              } else {
-                const int o = lds_base(j1 * SJ1 + (q * n + j2) * m);
-#pragma unroll
-                for (int i = 0; i < m; ++i) {
-                  PM[o + i] = om[rr][i];
-                  PA[o + i] = oa[rr][i];
-                }
-              }
-            }
-          }
-        } else {
-          for (int base = 0; base < NTASK; base += NT) {
-            const int task = base + tid;
-            int q, j2, j1;
-            if (!line_of(task, q, j2, j1)) continue;
-            const int o = lds_base(j1 * SJ1 + (q * n + j2) * m);
-            T sm[m], sa[m];
-            contract(task < FP, lds_base((j2 * n + j1) * RS + 2 * K * q), sm, sa);
-#pragma unroll
-            for (int i = 0; i < m; ++i) {
-              PM[o + i] = sm[i];
-              PA[o + i] = sa[i];
-            }
-          }
-        }
-      } else if constexpr (L::AL) {
+      if constexpr (L::AL) {
         // aliased: every line of the workgroup is read and contracted, then PM/PA overwrite X
         constexpr int NA = PPW * n * n, RA = (NA + NT - 1) / NT;
         T om[RA][m], oa[RA][m];
@@ -1194,7 +1861,7 @@ __device__ __forceinline__ void colour_pass_lines(T* __restrict__ smem, const T*
         apply_s<T, K>(in, w);
 #pragma unroll
         for (int i = 0; i < m; ++i)
-          st_lane(xo + (1 + i) * ld2, loff[rr], BND ? sol_scale * w[i] : fma(sol_scale, w[i], xpre[rr][i]));
+          st_lane(xo + (1 + i) * ld2, loff[rr], fma(sol_scale, w[i], xpre[rr][i]));
       }
     }
   } else {
@@ -1354,7 +2021,7 @@ __device__ __forceinline__ void colour_pass_lines(T* __restrict__ smem, const T*
         apply_s<T, K>(in, w);
 #pragma unroll
         for (int i = 0; i < m; ++i)
-          st_lane(xo + (1 + i) * ld1, loff[rr], BND ? sol_scale * w[i] : fma(sol_scale, w[i], xpre[rr][i]));
+          st_lane(xo + (1 + i) * ld1, loff[rr], fma(sol_scale, w[i], xpre[rr][i]));
       }
     }
   }
@@ -1669,82 +2336,97 @@ __device__ __forceinline__ void colour_pass_mfma3(float* __restrict__ smem, cons
   }
 }
 
-// LDS words of one workgroup of a colour pass.  The x2-first form (colour_pass_mult3) serves the 3D
-// multiplicative pass in FP64, where it measured 3-9% faster than the closure-through-LDS form; in
-// FP32 the two measured within 2% and the closure form is kept (its b loads stay within one node
-// plane per access).
 // Patches per workgroup of the matrix-core form (3D Q4, FP32, multiplicative), 256 threads.
 constexpr int kMfmaPPW = 4;
 template <int D, int K, typename T>
 struct HasMfmaForm {
   static constexpr bool value = D == 3 && K == 4 && sizeof(T) == 4;
 };
-template <int D, int K, typename T, int MODE>
-struct UsesMfma {
-  static constexpr bool value = HasMfmaForm<D, K, T>::value && MODE == kModeMfma;
-};
-// Default launch shape per form: patches per workgroup and threads.
-template <int D, int K, typename T, int MODE>
-struct ColourShape {
-  static constexpr bool kMfma = UsesMfma<D, K, T, MODE>::value;
-  static constexpr int PPW = kMfma ? kMfmaPPW : SmootherShape<D, K>::PPW;
-  static constexpr int NT = kMfma ? 256 : SmootherShape<D, K>::NT;
-};
-// Threads of a launch with PPW patches per workgroup (small launches take the vector form with the
-// latency shape).
-template <int D, int K, typename T, int MODE, int PPW>
-struct ColourNT {
-  static constexpr int value = UsesMfma<D, K, T, MODE>::value && PPW == kMfmaPPW ? 256
-                               : IsWide<D, K, T, MODE, PPW>::value               ? kWideNT
-                                                                                 : SmootherShape<D, K>::NT;
-};
 
-template <int D, int K, typename T, int MODE, int PPW>
-struct ColourLds {
-  static constexpr bool kMfma = UsesMfma<D, K, T, MODE>::value && PPW == kMfmaPPW;
-  static constexpr bool kMult3 = D == 3 && MODE == kModeMultiplicative && sizeof(T) == 8;
-  static constexpr int value = kMfma ? MfmaLds<K, PPW>::total
-                               : kMult3 ? Mult3Lds<K, PPW>::total
-                                        : SmootherLds<D, K, T, MODE == kModeAdditive || MODE == kModeZero, PPW,
-                                                      LinesAlias<D, K, T, MODE, PPW>::value,
-                                                      LinesPair<D, K, T, MODE, PPW>::value>::total;
+// What one workgroup of a launch runs, per mode and shape: SH is an EigShape for the eigenbasis form
+// (multiplicative and Boundary), else a LineShape.
+template <int PPWv, int NTv>
+struct LineShape {
+  static constexpr int PPW = PPWv, NT = NTv;
 };
-
-// One workgroup's share of a colour pass: the 3D multiplicative pass in FP64 contracts the closure
-// along x2 first; the other forms run the closure through LDS (colour_pass_lines).
-template <int D, int K, typename T, int MODE, int PPW>
-__device__ __forceinline__ void colour_pass_block(T* __restrict__ smem, const T* __restrict__ b, T* __restrict__ x,
-                                                  long long n1d, int p0, int p1, int p2, int cnt0, int cnt1,
-                                                  int groups0, T res_scale, T sol_scale, unsigned blk) {
-  if constexpr (ColourLds<D, K, T, MODE, PPW>::kMfma)
+template <int D, int K, typename T, int MODE, typename SH>
+struct ColourBody {
+  // the residual form of the 3D pass in FP64 contracts the closure along x2 first, where it measured 3-9%
+  // faster than the closure-through-LDS form; in FP32 the two measured within 2%
+  static constexpr bool kMult3 = D == 3 && MODE == kModeResidual && sizeof(T) == 8;
+  static constexpr int lds() {
+    if constexpr (kMult3) return Mult3Lds<K, SH::PPW>::total;
+    else return SmootherLds<D, K, T, MODE != kModeResidual, SH::PPW, LinesAlias<D, K, T, MODE, SH::PPW>::value,
+                            LinesPair<D, K, T, MODE, SH::PPW>::value>::total;
+  }
+  static constexpr int kLds = lds();
+  static __device__ __forceinline__ void run(T* smem, const T* b, T* x, long long n1d, int p0, int p1, int p2, int cnt0,
+                                             int cnt1, int groups0, T res_scale, T sol_scale, unsigned blk) {
+    if constexpr (kMult3)
+      colour_pass_mult3<K, T, SH::PPW>(smem, b, x, n1d, p0, p1, p2, cnt0, cnt1, groups0, res_scale, sol_scale, blk);
+    else
+      colour_pass_lines<D, K, T, MODE, SH::PPW>(smem, b, x, n1d, p0, p1, p2, cnt0, cnt1, groups0, res_scale, sol_scale,
+                                                blk);
+  }
+};
+template <int D, int K, typename T, int MODE, int PPW, int NT, bool AL>
+struct ColourBody<D, K, T, MODE, EigShape<PPW, NT, AL>> {
+  using SH = EigShape<PPW, NT, AL>;
+  static constexpr bool kPoison = MODE == kModeMultiplicative;
+  static constexpr int lds() {
+    if constexpr (D == 3) return EigLds3<K, SH>::total;
+    else return EigLds2<K, SH>::total;
+  }
+  static constexpr int kLds = lds();
+  static __device__ __forceinline__ void run(T* smem, const T* b, T* x, long long n1d, int p0, int p1, int p2, int cnt0,
+                                             int cnt1, int groups0, T, T sol_scale, unsigned blk) {
+    if constexpr (D == 3)
+      colour_pass_eig3<K, T, kPoison, SH>(smem, b, x, n1d, p0, p1, p2, cnt0, cnt1, groups0, sol_scale, blk);
+    else
+      colour_pass_eig2<K, T, kPoison, SH>(smem, b, x, n1d, p0, p1, cnt0, cnt1, groups0, sol_scale, blk);
+  }
+};
+template <int D, typename T, int MODE, int PPW>
+struct ColourBody<D, 1, T, MODE, Q1Shape<PPW>> {
+  static constexpr int kLds = 1;
+  static __device__ __forceinline__ void run(T*, const T* b, T* x, long long n1d, int p0, int p1, int p2, int cnt0,
+                                             int cnt1, int groups0, T res_scale, T sol_scale, unsigned blk) {
+    colour_pass_q1<D, T, MODE == kModeMultiplicative, PPW>(b, x, n1d, p0, p1, p2, cnt0, cnt1, groups0, res_scale,
+                                                           sol_scale, blk);
+  }
+};
+template <int D, int K, int PPW, int NT>
+struct ColourBody<D, K, float, kModeMfma, LineShape<PPW, NT>> {
+  static constexpr int kLds = MfmaLds<K, PPW>::total;
+  static __device__ __forceinline__ void run(float* smem, const float* b, float* x, long long n1d, int p0, int p1, int p2,
+                                             int cnt0, int cnt1, int groups0, float res_scale, float sol_scale,
+                                             unsigned blk) {
     colour_pass_mfma3<K, PPW>(smem, b, x, n1d, p0, p1, p2, cnt0, cnt1, groups0, res_scale, sol_scale, blk);
-  else if constexpr (ColourLds<D, K, T, MODE, PPW>::kMult3)
-    colour_pass_mult3<K, T, PPW>(smem, b, x, n1d, p0, p1, p2, cnt0, cnt1, groups0, res_scale, sol_scale, blk);
-  else
-    colour_pass_lines<D, K, T, MODE, PPW>(smem, b, x, n1d, p0, p1, p2, cnt0, cnt1, groups0, res_scale, sol_scale,
-                                          blk);
-}
+  }
+};
 
-template <int D, int K, typename T, int MODE, int PPW>
-__global__ __launch_bounds__((ColourNT<D, K, T, MODE, PPW>::value)) void colour_pass_kernel(
-    const T* __restrict__ b, T* __restrict__ x, long long n1d, int p0, int p1, int p2, int cnt0, int cnt1,
-    int groups0, T res_scale, T sol_scale) {
-  __shared__ __align__(16) T smem[ColourLds<D, K, T, MODE, PPW>::value];
-  colour_pass_block<D, K, T, MODE, PPW>(smem, b, x, n1d, p0, p1, p2, cnt0, cnt1, groups0, res_scale, sol_scale,
-                                  xcd_remap(blockIdx.x, gridDim.x));
+template <int D, int K, typename T, int MODE, typename SH>
+__global__ __launch_bounds__((SH::NT)) void colour_pass_kernel(const T* __restrict__ b, T* __restrict__ x,
+                                                               long long n1d, int p0, int p1, int p2, int cnt0,
+                                                               int cnt1, int groups0, T res_scale, T sol_scale) {
+  using Body = ColourBody<D, K, T, MODE, SH>;
+  __shared__ __align__(16) T smem[Body::kLds];
+  Body::run(smem, b, x, n1d, p0, p1, p2, cnt0, cnt1, groups0, res_scale, sol_scale,
+            xcd_remap(blockIdx.x, gridDim.x));
 }
 
 // Several colour passes of the same (dim, degree, precision, colour) on different vectors and
 // levels in one launch: entry e owns blocks [begin[e], begin[e+1]).
-template <int D, int K, typename T, int MODE, int PPW>
-__global__ __launch_bounds__((ColourNT<D, K, T, MODE, PPW>::value)) void colour_pass_group_kernel(ColourPassGroup grp) {
-  __shared__ __align__(16) T smem[ColourLds<D, K, T, MODE, PPW>::value];
+template <int D, int K, typename T, int MODE, typename SH>
+__global__ __launch_bounds__((SH::NT)) void colour_pass_group_kernel(ColourPassGroup grp) {
+  using Body = ColourBody<D, K, T, MODE, SH>;
+  __shared__ __align__(16) T smem[Body::kLds];
   const unsigned g = xcd_remap(blockIdx.x, gridDim.x);
   int e = 0;
   while (e + 1 < grp.n && (unsigned)grp.e[e + 1].block_begin <= g) ++e;
   const ColourPassDesc& d = grp.e[e];
-  colour_pass_block<D, K, T, MODE, PPW>(smem, (const T*)d.b, (T*)d.x, d.n1d, d.p[0], d.p[1], d.p[2], d.cnt0, d.cnt1,
-                                  d.groups0, (T)d.res_scale, (T)d.sol_scale, g - (unsigned)d.block_begin);
+  Body::run(smem, (const T*)d.b, (T*)d.x, d.n1d, d.p[0], d.p[1], d.p[2], d.cnt0, d.cnt1, d.groups0, (T)d.res_scale,
+            (T)d.sol_scale, g - (unsigned)d.block_begin);
 }
 
 // ------------------------------------------------------------------ host side
@@ -1772,18 +2454,36 @@ struct ColourGrid {
   }
 };
 
-template <int D, int K, typename T, int MODE, int PPW>
+template <int D, int K, typename T, int MODE, typename SH>
 static hipError_t launch_shape(const LevelGeom& g, const ColourGrid<D, K>& cg, const void* b, void* x,
                                hipStream_t st) {
-  constexpr int NT = ColourNT<D, K, T, MODE, PPW>::value;
   // Abar_h = h^(d-2) Abar_1 ; A_j,h^{-1} = h^(2-d) A_j,1^{-1}
   const T res_scale = (T)(D == 3 ? g.h : 1.0);
   const T sol_scale = (T)(D == 3 ? 1.0 / g.h : 1.0);
-  hipLaunchKernelGGL((colour_pass_kernel<D, K, T, MODE, PPW>), dim3((unsigned)cg.blocks), dim3(NT), 0, st,
+  hipLaunchKernelGGL((colour_pass_kernel<D, K, T, MODE, SH>), dim3((unsigned)cg.blocks), dim3(SH::NT), 0, st,
                      (const T*)b, (T*)x, g.n1d, cg.p[0], cg.p[1], cg.p[2], cg.cnt[0], cg.cnt[1], cg.groups0,
                      res_scale, sol_scale);
   return hipGetLastError();
 }
+
+// Shapes of a mode: the large one, and the small-launch one a launch takes when the large one would
+// give fewer than kMinBlocks workgroups.
+template <int D, int K, typename T, int MODE>
+struct ModeShapes {
+  using Large = LineShape<SmootherShape<D, K>::PPW, SmootherShape<D, K>::NT>;
+  using Small = LineShape<LatencyPPW<D, K>::value, SmootherShape<D, K>::NT>;
+  static constexpr long long kMinBlocks = kLatencyBlocks;
+};
+template <int D, int K, typename T>
+struct ModeShapes<D, K, T, kModeMultiplicative> {
+  using Large = typename EigShapes<D, K, T>::Large;
+  using Small = typename EigShapes<D, K, T>::Small;
+  static constexpr long long kMinBlocks = kEigWaves * 64 / Large::NT;
+};
+template <int D, int K, typename T>
+struct ModeShapes<D, K, T, kModeBoundary> : ModeShapes<D, K, T, kModeMultiplicative> {};
+using WideShape = LineShape<kWidePPW, kWideNT>;
+using MfmaShape = LineShape<kMfmaPPW, 256>;
 
 // The wide shape's launch: enough workgroups to leave the small-launch regime and few idle patch
 // slots at row ends.
@@ -1793,56 +2493,59 @@ static bool wide_fits(const ColourGrid<D, K>& cw) {
          (double)(cw.groups0 * kWidePPW - cw.cnt[0]) <= kWideIdle * (double)cw.cnt[0];
 }
 
+// True when a pass of this colour and level runs the matrix-core form: its launch has at least
+// kLatencyBlocks workgroups.  A packed launch must give each member the arithmetic of its stand-alone
+// pass, so that a result does not depend on the requests it is served with.
+template <int D, int K>
+static bool mfma_fits(const LevelGeom& g, int colour) {
+  return ColourGrid<D, K>(g, colour, kMfmaPPW).blocks >= kLatencyBlocks;
+}
+
 template <int D, int K, typename T, int MODE>
 static hipError_t launch_one(const LevelGeom& g, int colour, const void* b, void* x, hipStream_t st) {
-  constexpr int PPW = ColourShape<D, K, T, MODE>::PPW, LPPW = LatencyPPW<D, K>::value;
+  using Large = typename ModeShapes<D, K, T, MODE>::Large;
+  using Small = typename ModeShapes<D, K, T, MODE>::Small;
   if constexpr (HasWideForm<D, K, T, MODE>::value) {
     const ColourGrid<D, K> cw(g, colour, kWidePPW);
-    if (wide_fits(cw)) return launch_shape<D, K, T, MODE, kWidePPW>(g, cw, b, x, st);
+    if (wide_fits(cw)) return launch_shape<D, K, T, MODE, WideShape>(g, cw, b, x, st);
   }
-  const ColourGrid<D, K> cg(g, colour, PPW);
-  if (!cg.ok) return hipErrorInvalidConfiguration;
-  if (cg.blocks == 0) return hipSuccess;
-  if constexpr (LPPW < PPW) {
-    if (cg.blocks < kLatencyBlocks) {
-      const ColourGrid<D, K> cl(g, colour, LPPW);
-      if (!cl.ok) return hipErrorInvalidConfiguration;
-      return launch_shape<D, K, T, MODE, LPPW>(g, cl, b, x, st);
+  if constexpr (MODE == kModeMultiplicative || MODE == kModeBoundary) {
+    using Far = typename FarShape<D, K, T>::type;
+    if constexpr (!std::is_void<Far>::value) {
+      const ColourGrid<D, K> cf(g, colour, Far::PPW);
+      if (cf.ok && 2.0 * sizeof(T) * std::pow((double)g.n1d, D) > (double)kLastLevelCache)
+        return launch_shape<D, K, T, MODE, Far>(g, cf, b, x, st);
     }
   }
-  return launch_shape<D, K, T, MODE, PPW>(g, cg, b, x, st);
-}
-
-// True when a stand-alone pass of this colour and level runs the matrix-core form (launch_one: the
-// default shape, not the small-launch one).  A packed launch must give each member the arithmetic of
-// its stand-alone pass, so that a result does not depend on the requests it is served with.
-template <int D, int K, typename T, int MODE>
-static bool member_uses_mfma(const LevelGeom& g, int colour) {
-  if constexpr (!UsesMfma<D, K, T, MODE>::value) {
-    return false;
-  } else {
-    const ColourGrid<D, K> cg(g, colour, kMfmaPPW);
-    return cg.blocks >= kLatencyBlocks;
+  const ColourGrid<D, K> cg(g, colour, Large::PPW);
+  if (!cg.ok) return hipErrorInvalidConfiguration;
+  if (cg.blocks == 0) return hipSuccess;
+  if constexpr (!std::is_same<Small, Large>::value) {
+    if (cg.blocks < ModeShapes<D, K, T, MODE>::kMinBlocks) {
+      const ColourGrid<D, K> cl(g, colour, Small::PPW);
+      if (!cl.ok) return hipErrorInvalidConfiguration;
+      return launch_shape<D, K, T, MODE, Small>(g, cl, b, x, st);
+    }
   }
+  return launch_shape<D, K, T, MODE, Large>(g, cg, b, x, st);
 }
 
-// The members with mfma == member_uses_mfma, in launches of PPW patches per workgroup.
-template <int D, int K, typename T, int MODE, int PPW>
-static hipError_t launch_group_form(int colour, const ColourPassMember* mem, int nm, bool mfma, hipStream_t st) {
-  constexpr int NT = ColourNT<D, K, T, MODE, PPW>::value;
+// One launch per kMaxGroup of the members that `take` accepts, in workgroups of shape SH.
+template <int D, int K, typename T, int MODE, typename SH, typename F>
+static hipError_t launch_group_shape(int colour, const ColourPassMember* mem, int nm, hipStream_t st, F take) {
   ColourPassGroup grp;
   grp.n = 0;
   long long total = 0;
   auto flush = [&]() -> hipError_t {
     if (grp.n == 0) return hipSuccess;
-    hipLaunchKernelGGL((colour_pass_group_kernel<D, K, T, MODE, PPW>), dim3((unsigned)total), dim3(NT), 0, st, grp);
+    hipLaunchKernelGGL((colour_pass_group_kernel<D, K, T, MODE, SH>), dim3((unsigned)total), dim3(SH::NT), 0, st, grp);
     grp.n = 0;
     total = 0;
     return hipGetLastError();
   };
   for (int i = 0; i < nm; ++i) {
-    if (member_uses_mfma<D, K, T, MODE>(mem[i].g, colour) != mfma) continue;
-    const ColourGrid<D, K> cg(mem[i].g, colour, PPW);
+    if (!take(mem[i].g)) continue;
+    const ColourGrid<D, K> cg(mem[i].g, colour, SH::PPW);
     if (!cg.ok) return hipErrorInvalidConfiguration;
     if (cg.blocks == 0) continue;
     if (grp.n == kMaxGroup || total + cg.blocks > 0x7fffffffLL) {
@@ -1867,25 +2570,52 @@ static hipError_t launch_group_form(int colour, const ColourPassMember* mem, int
   return flush();
 }
 
-template <int D, int K, typename T, int MODE>
-static hipError_t launch_group(int colour, const ColourPassMember* mem, int nm, hipStream_t st) {
-  constexpr int PPW = SmootherShape<D, K>::PPW;
-  if constexpr (UsesMfma<D, K, T, MODE>::value) {
-    hipError_t e = launch_group_form<D, K, T, MODE, kMfmaPPW>(colour, mem, nm, true, st);
-    if (e != hipSuccess) return e;
-  }
-  return launch_group_form<D, K, T, MODE, PPW>(colour, mem, nm, false, st);
+// The members that `take` accepts: the small-launch shape when all of them together would give fewer
+// than kMinBlocks workgroups of the large one (the shapes give the same values bit for bit).
+template <int D, int K, typename T, int MODE, typename F>
+static hipError_t launch_group(int colour, const ColourPassMember* mem, int nm, hipStream_t st, F take) {
+  using Large = typename ModeShapes<D, K, T, MODE>::Large;
+  using Small = typename ModeShapes<D, K, T, MODE>::Small;
+  long long blocks = 0;
+  for (int i = 0; i < nm; ++i)
+    if (take(mem[i].g)) blocks += ColourGrid<D, K>(mem[i].g, colour, Large::PPW).blocks;
+  if (blocks < ModeShapes<D, K, T, MODE>::kMinBlocks)
+    return launch_group_shape<D, K, T, MODE, Small>(colour, mem, nm, st, take);
+  return launch_group_shape<D, K, T, MODE, Large>(colour, mem, nm, st, take);
+}
+
+// The kernel of kModeTail: the eigenbasis form without the loads of x^I, which gives the same values, where
+// the multiplicative pass has that form, else the multiplicative pass itself.
+template <typename T>
+constexpr int kPrec = sizeof(T) == 8 ? 0 : 1;
+template <int D, int K, typename T>
+struct HasEigenForm {
+  static constexpr bool value = K >= (D == 2 && sizeof(T) == 4 ? 5 : 3);  // has_eigen_form
+};
+template <int D, int K, typename T>
+constexpr int tail_mode() {
+  return HasEigenForm<D, K, T>::value ? kModeBoundary : K == 1 ? kModeMultiplicative : kModeResidual;
 }
 
 template <int D, int K, typename T>
 static hipError_t dispatch_mode(const LevelGeom& g, int mode, int colour, const void* b, void* x, hipStream_t st) {
   switch (mode) {
-    case kModeMultiplicative: return launch_one<D, K, T, kModeMultiplicative>(g, colour, b, x, st);
+    case kModeMultiplicative:
+      if constexpr (HasEigenForm<D, K, T>::value || K == 1)
+        if (K == 1 || eigen_step_fits(g, kPrec<T>)) return launch_one<D, K, T, kModeMultiplicative>(g, colour, b, x, st);
+      return dispatch_mode<D, K, T>(g, kModeResidual, colour, b, x, st);
     case kModeAdditive: return launch_one<D, K, T, kModeAdditive>(g, colour, b, x, st);
+    case kModeTail: return launch_one<D, K, T, tail_mode<D, K, T>()>(g, colour, b, x, st);
+    case kModeResidual:
+      return launch_one<D, K, T, K == 1 ? kModeMultiplicative : kModeResidual>(g, colour, b, x, st);
     case kModeBoundary: return launch_one<D, K, T, kModeBoundary>(g, colour, b, x, st);
     case kModeMfma:
-      if constexpr (HasMfmaForm<D, K, T>::value) return launch_one<D, K, T, kModeMfma>(g, colour, b, x, st);
-      return launch_one<D, K, T, kModeMultiplicative>(g, colour, b, x, st);
+      if constexpr (HasMfmaForm<D, K, T>::value) {
+        const ColourGrid<D, K> cm(g, colour, kMfmaPPW);
+        if (!cm.ok) return hipErrorInvalidConfiguration;
+        if (mfma_fits<D, K>(g, colour)) return launch_shape<D, K, T, kModeMfma, MfmaShape>(g, cm, b, x, st);
+      }
+      return dispatch_mode<D, K, T>(g, kModeMultiplicative, colour, b, x, st);
     case kModeZero:
       if (colour != 0) return hipErrorInvalidValue;  // only colour 0's closures tile the grid
       return launch_one<D, K, T, kModeZero>(g, colour, b, x, st);
@@ -1920,29 +2650,48 @@ hipError_t launch_colour_pass(const LevelGeom& g, int prec, int mode, int colour
   return g.dim == 2 ? dispatch_k<2>(g, prec, mode, colour, b, x, st) : dispatch_k<3>(g, prec, mode, colour, b, x, st);
 }
 
-template <int D, int K>
-static hipError_t group_prec(int prec, int mode, int colour, const ColourPassMember* m, int nm, hipStream_t st) {
-  if (mode == kModeAdditive)
-    return prec == 0 ? launch_group<D, K, double, kModeAdditive>(colour, m, nm, st)
-                     : launch_group<D, K, float, kModeAdditive>(colour, m, nm, st);
-  if (mode == kModeMultiplicative)
-    return prec == 0 ? launch_group<D, K, double, kModeMultiplicative>(colour, m, nm, st)
-                     : launch_group<D, K, float, kModeMultiplicative>(colour, m, nm, st);
-  if (mode == kModeBoundary)
-    return prec == 0 ? launch_group<D, K, double, kModeBoundary>(colour, m, nm, st)
-                     : launch_group<D, K, float, kModeBoundary>(colour, m, nm, st);
-  if (mode == kModeZero) {
-    if (colour != 0) return hipErrorInvalidValue;
-    return prec == 0 ? launch_group<D, K, double, kModeZero>(colour, m, nm, st)
-                     : launch_group<D, K, float, kModeZero>(colour, m, nm, st);
-  }
-  if (mode == kModeMfma) {
-    if constexpr (HasMfmaForm<D, K, float>::value)
-      if (prec == 1) return launch_group<D, K, float, kModeMfma>(colour, m, nm, st);
-    return prec == 0 ? launch_group<D, K, double, kModeMultiplicative>(colour, m, nm, st)
-                     : launch_group<D, K, float, kModeMultiplicative>(colour, m, nm, st);
+template <int D, int K, typename T>
+static hipError_t group_mode(int mode, int colour, const ColourPassMember* m, int nm, hipStream_t st) {
+  auto all = [](const LevelGeom&) { return true; };
+  switch (mode) {
+    case kModeMultiplicative:
+    case kModeResidual: {
+      auto eig = [mode](const LevelGeom& g) { return K == 1 || (mode == kModeMultiplicative && eigen_step_fits(g, kPrec<T>)); };
+      hipError_t e = hipSuccess;
+      if constexpr (HasEigenForm<D, K, T>::value || K == 1) e = launch_group<D, K, T, kModeMultiplicative>(colour, m, nm, st, eig);
+      if (e != hipSuccess) return e;
+      if constexpr (K > 1)
+        return launch_group<D, K, T, kModeResidual>(colour, m, nm, st, [&](const LevelGeom& g) { return !eig(g); });
+      return e;
+    }
+    case kModeAdditive: return launch_group<D, K, T, kModeAdditive>(colour, m, nm, st, all);
+    case kModeTail: return launch_group<D, K, T, tail_mode<D, K, T>()>(colour, m, nm, st, all);
+    case kModeBoundary: return launch_group<D, K, T, kModeBoundary>(colour, m, nm, st, all);
+    case kModeZero:
+      if (colour != 0) return hipErrorInvalidValue;
+      return launch_group<D, K, T, kModeZero>(colour, m, nm, st, all);
+    case kModeMfma: {
+      // the members whose own pass runs on the matrix cores, then the others as kModeMultiplicative
+      std::vector<ColourPassMember> rest;
+      if constexpr (HasMfmaForm<D, K, T>::value) {
+        auto fits = [colour](const LevelGeom& g) { return mfma_fits<D, K>(g, colour); };
+        hipError_t e = launch_group_shape<D, K, T, kModeMfma, MfmaShape>(colour, m, nm, st, fits);
+        if (e != hipSuccess) return e;
+        for (int i = 0; i < nm; ++i)
+          if (!fits(m[i].g)) rest.push_back(m[i]);
+      } else {
+        rest.assign(m, m + nm);
+      }
+      return group_mode<D, K, T>(kModeMultiplicative, colour, rest.data(), (int)rest.size(), st);
+    }
   }
   return hipErrorInvalidValue;
+}
+
+template <int D, int K>
+static hipError_t group_prec(int prec, int mode, int colour, const ColourPassMember* m, int nm, hipStream_t st) {
+  return prec == 0 ? group_mode<D, K, double>(mode, colour, m, nm, st)
+                   : group_mode<D, K, float>(mode, colour, m, nm, st);
 }
 
 template <int D>
@@ -2010,7 +2759,13 @@ bool colour_launches_ok(const LevelGeom& g, long long* nblk, std::string* why) {
     if (!colour_shape_ok<D, K, LatencyPPW<D, K>::value>(g, c, nblk, why)) return false;
     if constexpr (HasMfmaForm<D, K, float>::value)
       if (!colour_shape_ok<D, K, kMfmaPPW>(g, c, nblk, why)) return false;
-    if constexpr (HasWideForm<D, K, float, kModeMultiplicative>::value)
+    if (!colour_shape_ok<D, K, EigShapes<D, K, float>::Large::PPW>(g, c, nblk, why)) return false;
+    if (!colour_shape_ok<D, K, EigShapes<D, K, float>::Small::PPW>(g, c, nblk, why)) return false;
+    if (!colour_shape_ok<D, K, EigShapes<D, K, double>::Large::PPW>(g, c, nblk, why)) return false;
+    if (!colour_shape_ok<D, K, EigShapes<D, K, double>::Small::PPW>(g, c, nblk, why)) return false;
+    if constexpr (!std::is_void<typename FarShape<D, K, float>::type>::value)
+      if (!colour_shape_ok<D, K, FarShape<D, K, float>::type::PPW>(g, c, nblk, why)) return false;
+    if constexpr (HasWideForm<D, K, float, kModeResidual>::value)
       if (!colour_shape_ok<D, K, kWidePPW>(g, c, nblk, why)) return false;
   }
   return true;

@@ -88,13 +88,18 @@ double lagrange_deriv(const std::vector<double>& nodes, int i, double x) {
   return s;
 }
 
-bool generalized_eigen(int n, const std::vector<double>& A, const std::vector<double>& M,
-                       std::vector<double>& S, std::vector<double>& lam) {
+namespace {
+
+// A S = M S diag(lam), S^T M S = I by Cholesky and cyclic Jacobi in precision R; off2: squared relative
+// size of the off-diagonal part at which the sweeps stop.
+template <typename R>
+bool eigen_pairs(int n, const std::vector<R>& A, const std::vector<R>& M, R off2, std::vector<R>& S,
+                 std::vector<R>& lam) {
   // M = L L^T (Cholesky)
-  std::vector<double> L(n * n, 0.0);
+  std::vector<R> L(n * n, 0.0);
   for (int i = 0; i < n; ++i) {
     for (int j = 0; j <= i; ++j) {
-      double s = M[i * n + j];
+      R s = M[i * n + j];
       for (int p = 0; p < j; ++p) s -= L[i * n + p] * L[j * n + p];
       if (i == j) {
         if (s <= 0.0) return false;
@@ -105,54 +110,54 @@ bool generalized_eigen(int n, const std::vector<double>& A, const std::vector<do
     }
   }
   // C = L^{-1} A L^{-T}: first X = L^{-1} A (forward substitution per column), then C = X L^{-T}
-  std::vector<double> X(n * n), C(n * n);
+  std::vector<R> X(n * n), C(n * n);
   for (int c = 0; c < n; ++c)
     for (int i = 0; i < n; ++i) {
-      double s = A[i * n + c];
+      R s = A[i * n + c];
       for (int p = 0; p < i; ++p) s -= L[i * n + p] * X[p * n + c];
       X[i * n + c] = s / L[i * n + i];
     }
   for (int r = 0; r < n; ++r)
     for (int i = 0; i < n; ++i) {
-      double s = X[r * n + i];
+      R s = X[r * n + i];
       for (int p = 0; p < i; ++p) s -= C[r * n + p] * L[i * n + p];
       C[r * n + i] = s / L[i * n + i];
     }
   for (int i = 0; i < n; ++i)  // symmetrise rounding
     for (int j = 0; j < i; ++j) {
-      double s = 0.5 * (C[i * n + j] + C[j * n + i]);
+      R s = R(0.5) * (C[i * n + j] + C[j * n + i]);
       C[i * n + j] = C[j * n + i] = s;
     }
   // cyclic Jacobi: C = Q diag Q^T
-  std::vector<double> Q(n * n, 0.0);
+  std::vector<R> Q(n * n, 0.0);
   for (int i = 0; i < n; ++i) Q[i * n + i] = 1.0;
   for (int sweep = 0; sweep < 100; ++sweep) {
-    double off = 0.0, tot = 0.0;
+    R off = 0.0, tot = 0.0;
     for (int i = 0; i < n; ++i)
       for (int j = 0; j < n; ++j) {
         tot += C[i * n + j] * C[i * n + j];
         if (i != j) off += C[i * n + j] * C[i * n + j];
       }
-    if (off <= 1e-32 * tot) break;
+    if (off <= off2 * tot) break;
     for (int p = 0; p < n; ++p)
       for (int q = p + 1; q < n; ++q) {
-        double apq = C[p * n + q];
-        if (std::fabs(apq) < 1e-300) continue;
-        double theta = (C[q * n + q] - C[p * n + p]) / (2.0 * apq);
-        double t = (theta >= 0 ? 1.0 : -1.0) / (std::fabs(theta) + std::sqrt(theta * theta + 1.0));
-        double c = 1.0 / std::sqrt(t * t + 1.0), s = t * c;
+        R apq = C[p * n + q];
+        if (std::fabs(apq) < R(1e-300)) continue;
+        R theta = (C[q * n + q] - C[p * n + p]) / (R(2) * apq);
+        R t = (theta >= 0 ? R(1) : R(-1)) / (std::fabs(theta) + std::sqrt(theta * theta + R(1)));
+        R c = R(1) / std::sqrt(t * t + R(1)), s = t * c;
         for (int r = 0; r < n; ++r) {  // columns p, q
-          double crp = C[r * n + p], crq = C[r * n + q];
+          R crp = C[r * n + p], crq = C[r * n + q];
           C[r * n + p] = c * crp - s * crq;
           C[r * n + q] = s * crp + c * crq;
         }
         for (int r = 0; r < n; ++r) {  // rows p, q
-          double cpr = C[p * n + r], cqr = C[q * n + r];
+          R cpr = C[p * n + r], cqr = C[q * n + r];
           C[p * n + r] = c * cpr - s * cqr;
           C[q * n + r] = s * cpr + c * cqr;
         }
         for (int r = 0; r < n; ++r) {
-          double qrp = Q[r * n + p], qrq = Q[r * n + q];
+          R qrp = Q[r * n + p], qrq = Q[r * n + q];
           Q[r * n + p] = c * qrp - s * qrq;
           Q[r * n + q] = s * qrp + c * qrq;
         }
@@ -164,11 +169,18 @@ bool generalized_eigen(int n, const std::vector<double>& A, const std::vector<do
   S.assign(n * n, 0.0);
   for (int c = 0; c < n; ++c)
     for (int i = n - 1; i >= 0; --i) {
-      double s = Q[i * n + c];
+      R s = Q[i * n + c];
       for (int p = i + 1; p < n; ++p) s -= L[p * n + i] * S[p * n + c];
       S[i * n + c] = s / L[i * n + i];
     }
   return true;
+}
+
+}  // namespace
+
+bool generalized_eigen(int n, const std::vector<double>& A, const std::vector<double>& M,
+                       std::vector<double>& S, std::vector<double>& lam) {
+  return eigen_pairs<double>(n, A, M, 1e-32, S, lam);
 }
 
 namespace {
@@ -260,6 +272,82 @@ Tables1D build(int k) {
 }
 
 }  // namespace
+
+EigenBasis eigen_basis(int k, bool scaled) {
+  using R = long double;
+  const Tables1D& t = tables_for_degree(k);
+  const int m = 2 * k - 1, n = 2 * k + 1;
+  // the patch rows, made exactly mirror-symmetric (row i, column j <-> row m-1-i, column n-1-j)
+  std::vector<R> Ac(m * n), Mc(m * n), Ai(m * m), Mi(m * m), S, lam;
+  for (int i = 0; i < m; ++i)
+    for (int j = 0; j < n; ++j) {
+      const int o = (m - 1 - i) * n + n - 1 - j;
+      Ac[i * n + j] = R(0.5) * ((R)t.Ac[i * n + j] + (R)t.Ac[o]);
+      Mc[i * n + j] = R(0.5) * ((R)t.Mc[i * n + j] + (R)t.Mc[o]);
+      if (j > 0 && j < n - 1) {
+        Ai[i * m + j - 1] = Ac[i * n + j];
+        Mi[i * m + j - 1] = Mc[i * n + j];
+      }
+    }
+  if (!eigen_pairs<R>(m, Ai, Mi, 1e-40L, S, lam)) throw std::runtime_error("patch mass matrix not SPD");
+  std::vector<int> order;
+  for (int want = 1; want >= -1; want -= 2)
+    for (int a = 0; a < m; ++a) {
+      R se = 0, so = 0, nrm = 0;
+      for (int i = 0; i < m; ++i) {
+        const R u = S[i * m + a], w = S[(m - 1 - i) * m + a];
+        se = std::fmax(se, std::fabs(u - w));
+        so = std::fmax(so, std::fabs(u + w));
+        nrm = std::fmax(nrm, std::fabs(u));
+      }
+      const int par = se <= 1e-12L * nrm ? 1 : so <= 1e-12L * nrm ? -1 : 0;
+      if (par == 0) throw std::runtime_error("a patch eigenvector has no mirror parity");
+      if (par == want) order.push_back(a);
+    }
+  if ((int)order.size() != m || order.empty()) throw std::runtime_error("patch eigenvector parities");
+  EigenBasis e;
+  e.S.assign(m * m, 0.0);
+  e.Mt.assign(m * n, 0.0);
+  e.At.assign(m * n, 0.0);
+  e.lam.assign(m, 0.0);
+  e.be.assign(m, 0.0);
+  e.scale.assign(m, 1.0);
+  for (int a = 0; a < m; ++a) {
+    std::vector<R> col(m), row(n, 0), arow(n, 0);
+    for (int i = 0; i < m; ++i) col[i] = S[i * m + order[a]];
+    for (int j = 0; j < n; ++j)
+      for (int i = 0; i < m; ++i) {
+        row[j] += col[i] * Mc[i * n + j];
+        arow[j] += col[i] * Ac[i * n + j];
+      }
+    double best = -1.0;
+    for (int s = 0; s < (scaled ? 4096 : 1); ++s) {
+      const double c = std::exp2(s / 4096.0);
+      double ec = 0, nc = 0, er = 0, nr = 0;
+      for (int i = 0; i < m; ++i) {
+        const double v = c * (double)col[i], w = c * (double)row[i + 1];
+        ec += (v - (float)v) * (v - (float)v);
+        nc += v * v;
+        er += (w - (float)w) * (w - (float)w);
+        nr += w * w;
+      }
+      const double err = std::sqrt(ec / nc) + std::sqrt(er / nr);
+      if (best < 0 || err < best) {
+        best = err;
+        e.scale[a] = c;
+      }
+    }
+    const R c = e.scale[a];
+    e.lam[a] = (double)lam[order[a]];
+    e.be[a] = (double)(c * (arow[0] - lam[order[a]] * row[0]));
+    for (int i = 0; i < m; ++i) e.S[i * m + a] = (double)(c * col[i]);
+    for (int j = 0; j < n; ++j) {
+      e.Mt[a * n + j] = (double)(c * row[j]);
+      e.At[a * n + j] = (double)(c * arow[j]);
+    }
+  }
+  return e;
+}
 
 const Tables1D& tables_for_degree(int k) {
   static std::mutex mu;

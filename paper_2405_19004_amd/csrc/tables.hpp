@@ -33,6 +33,24 @@ struct Tables1D {
   std::vector<double> gauss_x, gauss_w;  // k+1 Gauss points / weights on [0,1]
 };
 
+// The eigenpairs as the colour pass uses them: even eigenvectors (under the mirror i -> m-1-i of the
+// symmetric patch pair) first, and column a multiplied by scale[a].  A scaled column solves the same
+// eigenproblem; the solve divides the scale out again (each 1D factor of A_j^{-1} carries
+// scale[a]^-2 on its eigenvalue sum).
+struct EigenBasis {
+  std::vector<double> S, lam, scale;  // m x m (column a scaled), m, m
+  std::vector<double> Mt;             // m x n: S^T M over the closure columns
+  std::vector<double> At;             // m x n: S^T A
+  std::vector<double> be;             // m: At - lam Mt at the left closure end
+};
+// scaled: choose each column's scale in [1, 2) so that the column and its row of S^T M lose least
+// when rounded to FP32 (the tables are what a smooth iterate is multiplied by, so their rounding is a
+// systematic error of every FP32 pass); otherwise all scales are 1.  Throws if an eigenvector has no
+// mirror parity.
+// Computed in extended precision: the pass does not correct a residual, so an error of these tables is
+// a relative error of its result.
+EigenBasis eigen_basis(int k, bool scaled);
+
 // Build (or fetch from a process-wide cache) the tables of degree k (1..kMaxDegree).
 const Tables1D& tables_for_degree(int k);
 
