@@ -904,8 +904,7 @@ __global__ __launch_bounds__(256) void restrict_plane_kernel(const T* __restrict
 // The in-plane part of the 3D scheme on the whole 2D grid: a workgroup owns a TX x TX coarse tile,
 // loads the fine nodes [2o - 2K, 2o + 2TX - 1] of both axes into LDS (fine boundary nodes as 0),
 // reduces along x0 (cell runs, restrict_run) and then along x1, and writes its coarse nodes, 0 on
-// the coarse boundary.  The tiles cover every coarse node; a non-null xz (the coarse iterate) is
-// zeroed on the same nodes.
+// the coarse boundary.  The tiles cover every coarse node.
 // Coarse cells per tile side, chosen so that the x0 stage (IX CX tasks: 220, 224, 252, 240, 200,
 // 240, 168 for degrees 1-7) is one round of the workgroup.  Tiles of about 28 coarse nodes per
 // side took up to 6 rounds: 2D V-cycles 1-5% slower at degrees 1-4 and 7, equal at 5.
@@ -922,8 +921,7 @@ struct Res2D {
 
 template <int K, typename T>
 __global__ __launch_bounds__(256) void restrict_tile2d_kernel(const T* __restrict__ rf, T* __restrict__ rc,
-                                                             T* __restrict__ xz, long long nf, long long nc,
-                                                             int tiles) {
+                                                             long long nf, long long nc, int tiles) {
   using S = Res2D<K, T>;
   constexpr int NT = S::NT, TX = S::TX, IX = S::IX, CX = S::CX, RUN = 2 * K, LPT = S::LPT, XS = S::XS, RS = S::RS;
   __shared__ T X[IX * XS];
@@ -970,7 +968,6 @@ __global__ __launch_bounds__(256) void restrict_tile2d_kernel(const T* __restric
       if (gx < nc && gy < nc) {
         const bool bnd = gx == 0 || gy == 0 || gx == nc - 1 || gy == nc - 1;
         rc[gy * nc + gx] = bnd ? T(0) : restrict_run<K, T>(in, a);
-        if (xz) xz[gy * nc + gx] = T(0);
       }
     }
   }
@@ -985,8 +982,8 @@ __global__ __launch_bounds__(256) void restrict_tile2d_kernel(const T* __restric
 #endif
 constexpr int kResCellsPerThread = VPS_RES_CPT;
 template <int K, typename T>
-__global__ __launch_bounds__(256) void restrict_z_kernel(const T* __restrict__ tz, T* __restrict__ rc, int nf, int nc,
-                                                        T* __restrict__ xz) {
+__global__ __launch_bounds__(256) void restrict_z_kernel(const T* __restrict__ tz, T* __restrict__ rc, int nf,
+                                                        int nc) {
   constexpr int NP = K + 1, RUN = 2 * K, CPT = kResCellsPerThread;
   using CT = gen::CellTables<T, K>;
   const int gx = blockIdx.x * 64 + threadIdx.x, gy = blockIdx.y * 4 + threadIdx.y;
@@ -1036,12 +1033,8 @@ __global__ __launch_bounds__(256) void restrict_z_kernel(const T* __restrict__ t
     for (int a = 0; a < K; ++a) {
       const int zc = K * C + a;
       st_lane(rc + zc * nc2, off, col && zc > 0 ? s[a] : T(0));
-      if (xz) st_lane(xz + zc * nc2, off, T(0));
     }
-    if (C == ncc - 1) {
-      st_lane(rc + (nc - 1) * nc2, off, T(0));  // the last coarse plane is a boundary plane
-      if (xz) st_lane(xz + (nc - 1) * nc2, off, T(0));
-    }
+    if (C == ncc - 1) st_lane(rc + (nc - 1) * nc2, off, T(0));  // the last coarse plane is a boundary plane
   }
 }
 
@@ -1315,7 +1308,7 @@ bool res_fits(const LevelGeom& fine) {
 }
 
 template <int D, int K, typename T>
-hipError_t res_launch(const LevelGeom& fine, const void* rf, void* rc, hipStream_t st, void* t, void* xz) {
+hipError_t res_launch(const LevelGeom& fine, const void* rf, void* rc, hipStream_t st, void* t) {
   const int nf = (int)fine.n1d, nc = (int)(K * (fine.ncells / 2) + 1);
   const int ncc = (nc - 1) / K;
   if (!res_fits<D, K, T>(fine)) return hipErrorInvalidConfiguration;
@@ -1329,11 +1322,11 @@ hipError_t res_launch(const LevelGeom& fine, const void* rf, void* rc, hipStream
                        0, st, (const T*)rf, (T*)t, (long long)nf, (long long)nc, tiles);
     hipLaunchKernelGGL((restrict_z_kernel<K, T>), dim3((unsigned)((nc + 63) / 64), (unsigned)((nc + 3) / 4),
                                                       (unsigned)ceil_div(ncc, kResCellsPerThread)),
-                       dim3(64, 4), 0, st, (const T*)t, (T*)rc, nf, nc, (T*)xz);
+                       dim3(64, 4), 0, st, (const T*)t, (T*)rc, nf, nc);
   } else {
     const int tiles = ceil_div(nc, Res2D<K, T>::TX);
     hipLaunchKernelGGL((restrict_tile2d_kernel<K, T>), dim3((unsigned)(tiles * tiles)), dim3(Res2D<K, T>::NT), 0, st,
-                       (const T*)rf, (T*)rc, (T*)xz, (long long)nf, (long long)nc, tiles);
+                       (const T*)rf, (T*)rc, (long long)nf, (long long)nc, tiles);
   }
   return hipGetLastError();
 }
@@ -1531,9 +1524,8 @@ hipError_t launch_prolongate_add(const LevelGeom& fine, int prec, const void* e,
   VPS_DISPATCH(pro_launch, fine, prec, e, xf, st);
 }
 
-hipError_t launch_restrict(const LevelGeom& fine, int prec, const void* rf, void* rc, void* t, hipStream_t st,
-                           void* xc_zero) {
-  VPS_DISPATCH(res_launch, fine, prec, rf, rc, st, t, xc_zero);
+hipError_t launch_restrict(const LevelGeom& fine, int prec, const void* rf, void* rc, void* t, hipStream_t st) {
+  VPS_DISPATCH(res_launch, fine, prec, rf, rc, st, t);
 }
 
 // ------------------------------------------- scratch of the allocation-free restriction

@@ -86,6 +86,18 @@ struct ColourPassMember {
 hipError_t launch_colour_pass_group(int dim, int k, int prec, int mode, int colour,
                                     const ColourPassMember* members, int n_members, hipStream_t st);
 
+// One smoothing step of corrections (the eigenbasis form without a look at old interior values; ascending colours, or
+// descending with reverse), or an additive step, on the members, all on the level g, several colours per launch.
+// span (1..dim): the unit of one workgroup (1: a row of patches along x0, with the two colours that differ in its
+// parity; dim: the grid, all colours).  clear (ascending only): x holds anything and counts as 0.
+hipError_t launch_smooth_fused(const LevelGeom& g, int prec, bool additive, int span, bool reverse, bool clear,
+                               const ColourPassMember* members, int n_members, hipStream_t st);
+// The span of a step on a level; 0: one colour per launch.
+int fused_span(const LevelGeom& g, int prec, bool additive);
+// x = A_1^{-1} b on level 1 for every member, in FP64 arithmetic.
+hipError_t launch_coarse_solve(int dim, int k, int prec, const ColourPassMember* members, int n_members,
+                               hipStream_t st);
+
 // smoother.hip
 hipError_t launch_colour_pass(const LevelGeom& g, int prec, int mode, int colour, const void* b, void* x,
                               hipStream_t st);
@@ -105,10 +117,7 @@ hipError_t launch_residual_norm2(const LevelGeom& g, const double* x, const doub
                                  long long max_parts, double* out, hipStream_t st, bool* fused);
 // Restriction P^T of a fine-level vector (fine boundary entries ignored, coarse boundary written 0);
 // t is scratch of restrict_scratch_elems(fine) elements (none in 2D: one kernel, no intermediate).
-// A non-null xc_zero (a coarse-level vector) is set to 0 as well, which saves the V-cycle a fill
-// launch per level.
-hipError_t launch_restrict(const LevelGeom& fine, int prec, const void* rf, void* rc, void* t, hipStream_t st,
-                           void* xc_zero = nullptr);
+hipError_t launch_restrict(const LevelGeom& fine, int prec, const void* rf, void* rc, void* t, hipStream_t st);
 inline long long restrict_scratch_elems(int dim, int k, int fine_level) {
   const long long nf = (long long)k * (1LL << fine_level) + 1, nc = (long long)k * (1LL << (fine_level - 1)) + 1;
   return dim == 2 ? 0 : nf * nc * nc;
@@ -136,8 +145,6 @@ hipError_t launch_l2_error(const LevelGeom& g, const double* x, const double* V,
 // vector.hip
 int reduction_parts();  // partial slots the reductions use (pairs: 2x this many doubles)
 hipError_t launch_fill(int prec, void* x, long long n, double v, hipStream_t st);
-// dst = (double)src, zero = 0 (n entries each)
-hipError_t launch_widen_zero(const float* src, double* dst, double* zero, long long n, hipStream_t st);
 hipError_t launch_cast(int from_prec, const void* src, void* dst, long long n, hipStream_t st);
 // dst = interior of src, out = |dst|^2, *bad |= non-finite entries; optionally dst32 = (float)dst
 // and zero = 0 over the same range

@@ -82,11 +82,6 @@ Plan plan(int dim, int k, int L, unsigned flags) {
       if (lvl >= 2 && dim == 3) pl.sizes.push_back((size_t)restrict_scratch_elems(dim, k, lvl) * es);  // restriction scratch
     }
   }
-  if (h32) {
-    const size_t N1 = (size_t)level_nodes(dim, k, 1);
-    pl.sizes.push_back(N1 * 8);
-    pl.sizes.push_back(N1 * 8);
-  }
   if (solver) {
     // r, z, p, q; z only with the FP64 hierarchy: a mixed solve reads the FP32 V-cycle output
     const size_t N = (size_t)level_nodes(dim, k, L);
@@ -179,10 +174,6 @@ Status create_problem(int dim, int k, int L, unsigned flags, hipStream_t st, Pro
       if (lvl >= 2 && dim == 3) B.t[prec] = p->allocs[idx++];
     }
   }
-  if (h32) {
-    p->c64_b = (double*)p->allocs[idx++];
-    p->c64_x = (double*)p->allocs[idx++];
-  }
   if (solver) {
     p->r = (double*)p->allocs[idx++];
     if (h64) p->z = (double*)p->allocs[idx++];
@@ -234,6 +225,15 @@ static int step_mode(int mode, const LevelGeom& g, int prec, int i, int c, bool 
 
 Status smoother(Problem* p, int level, int prec, int mode, bool reverse, const void* b, void* x, bool x_zero,
                 StepUse use) {
+  const LevelGeom& g = p->geom(level);
+  // small levels: several colours per launch
+  if ((mode == kModeMultiplicative && use == StepUse::kCorrection) || mode == kModeAdditive) {
+    if (const int span = fused_span(g, prec, mode == kModeAdditive)) {
+      const ColourPassMember m{g, b, x};
+      VPS_HIP(launch_smooth_fused(g, prec, mode == kModeAdditive, span, reverse, x_zero, &m, 1, p->stream));
+      return Status::ok();
+    }
+  }
   const int nc = 1 << p->dim;
   for (int i = 0; i < nc; ++i) {
     const int c = reverse ? nc - 1 - i : i;
@@ -243,17 +243,9 @@ Status smoother(Problem* p, int level, int prec, int mode, bool reverse, const v
 }
 
 Status coarse_solve(Problem* p, int prec, const void* b, void* x) {
-  const LevelGeom& g = p->geom(1);
-  const long long N = p->lv[1].N;
-  if (prec == 0) {
-    VPS_HIP(launch_fill(0, x, N, 0.0, p->stream));
-    VPS_HIP(launch_colour_pass(g, 0, kModeMultiplicative, 0, b, x, p->stream));
-    return Status::ok();
-  }
-  if (!p->c64_b) return Status{-1, "FP32 coarse solve needs the FP32 hierarchy"};
-  VPS_HIP(launch_widen_zero(static_cast<const float*>(b), p->c64_b, p->c64_x, N, p->stream));
-  VPS_HIP(launch_colour_pass(g, 0, kModeMultiplicative, 0, p->c64_b, p->c64_x, p->stream));
-  VPS_HIP(launch_cast(0, p->c64_x, x, N, p->stream));
+  if (prec == 1 && !p->has(1)) return Status{-1, "FP32 coarse solve needs the FP32 hierarchy"};
+  const ColourPassMember m{p->geom(1), b, x};
+  VPS_HIP(launch_coarse_solve(p->dim, p->k, prec, &m, 1, p->stream));
   return Status::ok();
 }
 
@@ -265,12 +257,12 @@ Status vcycle_top(Problem* p, int prec, int top, const void* bT, void* xT, bool 
   for (int lvl = top; lvl >= 2; --lvl) {
     const void* b = lvl == top ? bT : p->lv[lvl].b[prec];
     void* x = lvl == top ? xT : p->lv[lvl].x[prec];
-    // below the top, x starts from 0: the restriction into this level zeroed it
+    // below the top, x starts from 0 (the first pass writes every node)
     const bool zero = lvl < top || top_zero;
     VPS_TRY(smoother(p, lvl, prec, vcycle_mode(p), false, b, x, zero, zero ? StepUse::kCorrection : StepUse::kStep));
     VPS_HIP(launch_operator(p->geom(lvl), prec, x, b, p->lv[lvl].r[prec], p->stream));
     VPS_HIP(launch_restrict(p->geom(lvl), prec, p->lv[lvl].r[prec], p->lv[lvl - 1].b[prec], p->lv[lvl].t[prec],
-                            p->stream, lvl - 1 >= 2 ? p->lv[lvl - 1].x[prec] : nullptr));
+                            p->stream));
   }
   VPS_TRY(coarse_solve(p, prec, p->lv[1].b[prec], p->lv[1].x[prec]));
   // ascend
@@ -392,9 +384,15 @@ Status vcycle_group(Problem* const* ps, int n, int prec, const void* const* bL, 
     mem.clear();
     for (int i = 0; i < n; ++i)
       if (ps[i]->L >= lvl) mem.push_back({ps[i]->geom(lvl), level_b(i, lvl), level_x(i, lvl)});
+    const StepUse use = top_zero ? StepUse::kCorrection : post ? StepUse::kLast : StepUse::kStep;
+    if (vcycle_mode(ps[0]) == kModeMultiplicative && use == StepUse::kCorrection) {
+      if (const int span = fused_span(mem[0].g, prec, false)) {
+        VPS_HIP(launch_smooth_fused(mem[0].g, prec, false, span, reverse, x_zero, mem.data(), (int)mem.size(), st));
+        return Status::ok();
+      }
+    }
     for (int j = 0; j < nc; ++j) {
       const int c = reverse ? nc - 1 - j : j;
-      const StepUse use = top_zero ? StepUse::kCorrection : post ? StepUse::kLast : StepUse::kStep;
       const int mode = step_mode(vcycle_mode(ps[0]), mem[0].g, prec, j, c, reverse, x_zero, use);
       if (mode == kSmoothSeparate) {
         // residual of every member, then the packed local solves on it
@@ -413,17 +411,18 @@ Status vcycle_group(Problem* const* ps, int n, int prec, const void* const* bL, 
     return Status::ok();
   };
   for (int lvl = Lmax; lvl >= 2; --lvl) {
-    // levels below a member's top start from 0 (the restriction into them zeroed x)
+    // levels below a member's top start from 0 (the first pass writes every node)
     VPS_TRY(smooth(lvl, false, top_zero, false));
     for (int i = 0; i < n; ++i) {
       if (ps[i]->L < lvl) continue;
       Problem* p = ps[i];
       VPS_HIP(launch_operator(p->geom(lvl), prec, level_x(i, lvl), level_b(i, lvl), p->lv[lvl].r[prec], st));
-      VPS_HIP(launch_restrict(p->geom(lvl), prec, p->lv[lvl].r[prec], p->lv[lvl - 1].b[prec], p->lv[lvl].t[prec], st,
-                              lvl - 1 >= 2 ? p->lv[lvl - 1].x[prec] : nullptr));
+      VPS_HIP(launch_restrict(p->geom(lvl), prec, p->lv[lvl].r[prec], p->lv[lvl - 1].b[prec], p->lv[lvl].t[prec], st));
     }
   }
-  for (int i = 0; i < n; ++i) VPS_TRY(coarse_solve(ps[i], prec, level_b(i, 1), level_x(i, 1)));
+  mem.clear();
+  for (int i = 0; i < n; ++i) mem.push_back({ps[i]->geom(1), level_b(i, 1), level_x(i, 1)});
+  VPS_HIP(launch_coarse_solve(dim, k, prec, mem.data(), n, st));
   for (int lvl = 2; lvl <= Lmax; ++lvl) {
     for (int i = 0; i < n; ++i)
       if (ps[i]->L >= lvl)

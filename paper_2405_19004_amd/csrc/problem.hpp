@@ -30,8 +30,6 @@ struct Problem {
   unsigned flags = 0;
   hipStream_t stream = nullptr;
   std::vector<LevelBuffers> lv;  // index 0 unused, 1..L
-  double* c64_b = nullptr;       // FP64 coarse pair used by the FP32 V-cycle
-  double* c64_x = nullptr;
   // CG state
   double *r = nullptr, *z = nullptr, *p = nullptr, *q = nullptr;
   double* sc = nullptr;       // scalar block (kScCount doubles)

@@ -100,7 +100,7 @@ constexpr int pad32(int v, int r) { return v + ((r - v) % 32 + 32) % 32; }
 // LDS layouts.  Every transpose buffer puts the loop axis of the stage that reads it outermost,
 // so the reading lanes touch consecutive words; the outer stride is padded (mod 32) so that the
 // writing lanes of the previous stage also fall into distinct banks.
-template <int D, int K, typename T, bool ADD, int PPWv, bool ALIASv = false, bool PAIRv = false>
+template <int D, int K, typename T, int PPWv, bool ALIASv = false, bool PAIRv = false>
 struct SmootherLds {
   static constexpr int n = 2 * K + 1, m = 2 * K - 1;
   static constexpr int PPW = PPWv;
@@ -115,9 +115,9 @@ struct SmootherLds {
   static constexpr int SI0 = pad32(PPW * m * m, 1);          // W5 [i0][q][a2][a1]
   static constexpr int SA1 = pad32(PPW * m * m, 1);          // W6 [a1][q][a2][i0]
   static constexpr int SA2 = pad32(PPW * m * m, m);          // W7 [a2][q][i1][i0]
-  static constexpr int X3 = ADD ? 0 : n * n * RS;
-  static constexpr int P3 = ADD ? 0 : 2 * n * SJ1;
-  static constexpr int UV3 = ADD ? 0 : 2 * n * SJ2;
+  static constexpr int X3 = n * n * RS;
+  static constexpr int P3 = 2 * n * SJ1;
+  static constexpr int UV3 = 2 * n * SJ2;
   static constexpr int A3 = P3 > m * SI1 ? (P3 > m * SA1 ? P3 : m * SA1) : (m * SI1 > m * SA1 ? m * SI1 : m * SA1);
   static constexpr int B3a = X3 > UV3 ? X3 : UV3;
   static constexpr int B3b = m * SI0 > m * SA2 ? m * SI0 : m * SA2;
@@ -126,15 +126,15 @@ struct SmootherLds {
   static constexpr int T1 = pad32(PPW * m, (m * PPW) % 32);  // P2  [j1][q][i0]  (PM, PA)
   static constexpr int T0 = pad32(PPW * m, 1);               // W   [i0][q][a1]
   static constexpr int TA = pad32(PPW * m, 1);               // W2  [a1][q][i0]
-  static constexpr int X2 = ADD ? 0 : n * RS;
-  static constexpr int P2 = ADD ? 0 : 2 * n * T1;
+  static constexpr int X2 = n * RS;
+  static constexpr int P2 = 2 * n * T1;
   static constexpr int A2 = P2 > m * TA ? P2 : m * TA;
   static constexpr int B2 = X2 > m * T0 ? X2 : m * T0;
   // ---- aliased 3D layout (multiplicative): the closure X, PM/PA and U/V all start at word 0 (the x0
   // and x1 stages read their inputs into registers and the workgroup synchronises before they
   // write), the x2 and x0 diagonalisation outputs (W4, W6) follow U/V, the x1 ones (W5, W7) start
   // at 0 again once U/V is dead
-  static constexpr bool AL = ALIASv && D == 3 && !ADD;
+  static constexpr bool AL = ALIASv && D == 3;
   static constexpr int W46 = m * SI1 > m * SA1 ? m * SI1 : m * SA1;
   static constexpr int W57 = m * SI0 > m * SA2 ? m * SI0 : m * SA2;
   static constexpr int AL3a = X3 > P3 ? X3 : P3;
@@ -144,14 +144,14 @@ struct SmootherLds {
   // stage), W4 also over U/V (the x2 stage synchronises before it writes), W5 and W7 after W4/W6
   static constexpr bool PR = PAIRv && AL;
   static constexpr int SJP = pad32(2 * PPW * n * m, 30);
-  static constexpr int PP3 = ADD ? 0 : n * SJP;
+  static constexpr int PP3 = n * SJP;
   static constexpr int PR3a = X3 > PP3 ? X3 : PP3;
   static constexpr int PR3b = UV3 > W46 + W57 ? UV3 : W46 + W57;
   static constexpr int PR3 = PR3a > PR3b ? PR3a : PR3b;
   // ---- aliased 2D layout (multiplicative): X, PM/PA and the x1 stage's output W start at word 0
   // (the x0 and x1 stages compute every line, the workgroup synchronises, then they write over
   // their inputs); W2 follows W
-  static constexpr bool AL2 = ALIASv && D == 2 && !ADD;
+  static constexpr bool AL2 = ALIASv && D == 2;
   static constexpr int AL2a = X2 > P2 ? X2 : P2;
   static constexpr int AL2T = AL2a > m * T0 + m * TA ? AL2a : m * T0 + m * TA;
   static constexpr int total = D == 3 ? (PR ? PR3 : AL ? AL3 : A3 + B3) : (AL2 ? AL2T : A2 + B2);
@@ -349,12 +349,14 @@ struct EigLds3 {
 //   D  lines (q, a2, i0)         x1: S                                      -> W7
 //   E  lines (i1, q, i0)         x2: S, plus c, straight to global
 // The lists of stages A and B are cut into whole waves per kind of task, so no wave mixes two kinds.
+// tid: the thread's index in its team of SH::NT threads (the whole workgroup, or one of several that take
+// different blocks and meet at the barriers); active: whether the team has a block.
 // POISON: a non-finite old interior value makes the patch's result non-finite, as the residual form
 // does (x^I enters through one multiply-add by zero per node); without it x^I is never read.
 template <int K, typename T, bool POISON, typename SH>
 __device__ __forceinline__ void colour_pass_eig3(T* __restrict__ smem, const T* __restrict__ b, T* __restrict__ x,
                                                  long long n1d, int p0, int p1, int p2, int cnt0, int cnt1,
-                                                 int groups0, T sol_scale, unsigned blk) {
+                                                 int groups0, T sol_scale, unsigned blk, int tid, bool active) {
   constexpr int n = 2 * K + 1, m = 2 * K - 1, mm = m * m;
   constexpr int PPW = SH::PPW, NT = SH::NT, NW = NT / 64;
   static_assert(NT % 64 == 0, "whole waves");
@@ -364,10 +366,10 @@ __device__ __forceinline__ void colour_pass_eig3(T* __restrict__ smem, const T* 
   constexpr int NF = 2 * PPW;  // x0 faces
 
   const ColourBlock cb = colour_block<3, K, PPW>(blk, p0, p1, p2, cnt0, cnt1, groups0);
-  const int P = cb.count;
+  const int P = active ? cb.count : 0;  // an idle team only meets the barriers
   const long long s0 = cb.s0, s1 = cb.s1, s2 = cb.s2;
   const long long n1d2 = n1d * n1d;
-  const int tid = threadIdx.x, lane = tid & 63;
+  const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int seg = 2 * K * P + 1;  // valid closure columns along x0
   const int ld1 = (int)n1d;
@@ -745,7 +747,7 @@ struct EigLds2 {
 template <int K, typename T, bool POISON, typename SH>
 __device__ __forceinline__ void colour_pass_eig2(T* __restrict__ smem, const T* __restrict__ b, T* __restrict__ x,
                                                  long long n1d, int p0, int p1, int cnt0, int cnt1, int groups0,
-                                                 T sol_scale, unsigned blk) {
+                                                 T sol_scale, unsigned blk, int tid, bool active) {
   constexpr int n = 2 * K + 1, m = 2 * K - 1;
   constexpr int PPW = SH::PPW, NT = SH::NT, NW = NT / 64;
   static_assert(NT % 64 == 0, "whole waves");
@@ -755,9 +757,9 @@ __device__ __forceinline__ void colour_pass_eig2(T* __restrict__ smem, const T* 
   constexpr int NF = 2 * PPW;  // x0 faces
 
   const ColourBlock cb = colour_block<2, K, PPW>(blk, p0, p1, 0, cnt0, cnt1, groups0);
-  const int P = cb.count;
+  const int P = active ? cb.count : 0;  // an idle team only meets the barriers
   const long long s0 = cb.s0, s1 = cb.s1;
-  const int tid = threadIdx.x, lane = tid & 63;
+  const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int seg = 2 * K * P + 1;
   const int ld1 = (int)n1d;
@@ -941,18 +943,18 @@ __device__ __forceinline__ void colour_pass_eig2(T* __restrict__ smem, const T* 
 template <int D, typename T, bool OLD, int PPW>
 __device__ __forceinline__ void colour_pass_q1(const T* __restrict__ b, T* __restrict__ x, long long n1d, int p0, int p1,
                                                int p2, int cnt0, int cnt1, int groups0, T res_scale, T sol_scale,
-                                               unsigned blk) {
+                                               unsigned blk, int tid, bool active) {
   using PT = gen::PatchTables<T, 1>;
   constexpr int n = 3, J2 = D == 3 ? n : 1;
   const ColourBlock cb = colour_block<D, 1, PPW>(blk, p0, p1, p2, cnt0, cnt1, groups0);
-  const int q = threadIdx.x, seg = 2 * cb.count + 1;
+  const int q = tid, seg = 2 * cb.count + 1;
   const long long n1d2 = n1d * n1d, origin = (D == 3 ? cb.s2 * n1d2 : 0) + cb.s1 * n1d + cb.s0;
   const unsigned span = (unsigned)((D == 3 ? 2 * n1d2 : 0) + 2 * n1d + seg) * (unsigned)sizeof(T);
   const Window<T> xw(x + origin, span), bw(b + origin, span);
   const bool lo0 = cb.s0 == 0, hi0 = cb.s0 + seg - 1 == n1d - 1;
   const bool edge1[2] = {cb.s1 == 0, cb.s1 + 2 == n1d - 1};
   const bool edge2[2] = {D == 3 && cb.s2 == 0, D == 3 && cb.s2 + 2 == n1d - 1};
-  if (q >= cb.count) return;
+  if (!active || q >= cb.count) return;
   // the patch's columns 2q, 2q + 1, 2q + 2; Dirichlet columns read as 0
   unsigned off[n];
 #pragma unroll
@@ -1039,6 +1041,230 @@ struct FarShape {
   using type = void;
 };
 template <> struct FarShape<3, 7, float> { using type = EigShape<3, 512, true>; };
+// ------------------------------------------------------------------ passes without a residual
+//
+// Additive pass x^I += A_j^{-1} b^I; ZERO: the first colour of a step on x = 0 (kModeZero), which stores
+// A_j^{-1} b^I on the patch interiors and 0 on the rest of its closures and reads no x.  The eigenbasis pass
+// without faces: the same line stages, row-ordered global accesses and team arguments.
+template <int D, int K, typename SH>
+struct AddLds {
+  static constexpr int PPW = SH::PPW, m = 2 * K - 1, mm = m * m;
+  static constexpr int SI1 = pad32(PPW * mm, m);  // BT [i1][q][a2][i0]
+  static constexpr int SI0 = pad32(PPW * mm, 1);  // W5 [i0][q][a2][a1]
+  static constexpr int SA1 = pad32(PPW * mm, 1);  // W6 [a1][q][a2][i0]
+  static constexpr int SA2 = pad32(PPW * mm, m);  // W7 [a2][i1][q][i0]
+  static constexpr int T0 = pad32(PPW * m, 1);    // 2D: W [i0][q][a1], W2 [a1][q][i0]
+  static constexpr int A = D == 3 ? m * max_of(SI1, SA1) : m * T0, B = D == 3 ? m * max_of(SI0, SA2) : m * T0;
+  static constexpr int total = A + B;
+};
+
+template <int D, int K, typename T, bool ZERO, typename SH>
+__device__ __forceinline__ void colour_pass_add(T* __restrict__ smem, const T* __restrict__ b, T* __restrict__ x,
+                                                long long n1d, int p0, int p1, int p2, int cnt0, int cnt1, int groups0,
+                                                T sol_scale, unsigned blk, int tid, bool active) {
+  constexpr int n = 2 * K + 1, m = 2 * K - 1, mm = m * m;
+  constexpr int PPW = SH::PPW, NT = SH::NT, NB = D == 3 ? PPW * mm : PPW * m, RC = (NB + NT - 1) / NT;
+  using L = AddLds<D, K, SH>;
+  const ColourBlock cb = colour_block<D, K, PPW>(blk, p0, p1, p2, cnt0, cnt1, groups0);
+  const int P = active ? cb.count : 0;
+  const long long n1d2 = n1d * n1d, origin = (D == 3 ? cb.s2 * n1d2 : 0) + cb.s1 * n1d + cb.s0;
+  const int seg = 2 * K * P + 1, ld1 = (int)n1d;
+  const unsigned span = (unsigned)((D == 3 ? 2 * K * n1d2 : 0) + 2 * K * n1d + seg) * (unsigned)sizeof(T);
+  const Window<T> xw(x + origin, span), bw(b + origin, span);
+  // interior planes (3D) or rows (2D) along the slowest axis
+  unsigned pl[m];
+#pragma unroll
+  for (int i = 0; i < m; ++i)
+    pl[i] = __builtin_amdgcn_readfirstlane((unsigned)((1 + i) * (D == 3 ? n1d2 : n1d)) * (unsigned)sizeof(T));
+  // line t of the slowest axis, (i1, q, i0) in 3D and (q, i0) in 2D: byte offset inside its plane or row
+  auto line = [&](int t, int& q, int& i1, int& i0, unsigned& off) -> bool {
+    if constexpr (D == 3) {
+      i1 = div_small<PPW * m>(t);
+      const int r = t - i1 * (PPW * m);
+      q = div_small<m>(r);
+      i0 = r - q * m;
+      off = (unsigned)((1 + i1) * ld1 + 2 * K * q + 1 + i0) * (unsigned)sizeof(T);
+    } else {
+      q = div_small<m>(t);
+      i1 = 0;
+      i0 = t - q * m;
+      off = (unsigned)(2 * K * q + 1 + i0) * (unsigned)sizeof(T);
+    }
+    return t < NB && q < P;
+  };
+  T v[RC][m], xo[RC][m], iv[RC][m];
+#pragma unroll
+  for (int rr = 0; rr < RC; ++rr) {
+    int q, i1, i0;
+    unsigned off;
+    if (line(rr * NT + tid, q, i1, i0, off)) {
+#pragma unroll
+      for (int i = 0; i < m; ++i) v[rr][i] = bw.load(pl[i], off);
+      if constexpr (!ZERO) {
+#pragma unroll
+        for (int i = 0; i < m; ++i) xo[rr][i] = xw.load(pl[i], off);
+      }
+    }
+  }
+  if constexpr (ZERO) {
+    // 0 on every closure node that is not a patch interior (neighbouring workgroups write the same zeros on shared
+    // faces; no interior of the colour lies there): the face rows whole, on the others the columns between patches
+    constexpr int RS = 2 * K * PPW + 1, NFR = D == 3 ? 4 * (n - 1) : 2, NIR = D == 3 ? mm : m;
+    constexpr int NZF = NFR * RS, NZ = NZF + NIR * (PPW + 1);
+    for (int w = tid; w < NZ && P > 0; w += NT) {
+      int j1, j2 = 0, c;
+      if (w < NZF) {
+        const int f = w / RS;
+        c = w - f * RS;
+        if constexpr (D == 3) {
+          if (f < 2 * n) {
+            j2 = f < n ? 0 : n - 1;
+            j1 = f < n ? f : f - n;
+          } else {
+            j2 = 1 + (f - 2 * n) / 2;
+            j1 = (f & 1) ? n - 1 : 0;  // f - 2n and f have the same parity (2n even)
+          }
+        } else {
+          j1 = f == 0 ? 0 : n - 1;
+        }
+      } else {
+        const int u = w - NZF, r = u / (PPW + 1);
+        c = 2 * K * (u - r * (PPW + 1));
+        if constexpr (D == 3) {
+          j2 = 1 + r / m;
+          j1 = 1 + (r - (r / m) * m);
+        } else {
+          j1 = 1 + r;
+        }
+      }
+      if (c < seg) xw.store(0, (unsigned)((D == 3 ? j2 * n1d2 : 0) + j1 * n1d + c) * (unsigned)sizeof(T), T(0));
+    }
+  }
+  // the lane's reciprocal eigenvalue sums: fetched with the first loads where the registers allow it
+  constexpr bool kEarly = RC * m * sizeof(T) <= 104;
+  auto fetch_inv = [&]() {
+    const DevTables<T>& tb = tab_fresh<T>(K);
+#pragma unroll
+    for (int rr = 0; rr < RC; ++rr) {
+      const int t = rr * NT + tid, r = D == 3 ? t - div_small<mm>(t) * mm : t - div_small<m>(t) * m;
+#pragma unroll
+      for (int a = 0; a < m; ++a) iv[rr][a] = D == 3 ? tb.inv3[r * m + a] : tb.inv2[r * m + a];
+    }
+  };
+  if constexpr (kEarly) fetch_inv();
+  // ---- S^T along the slowest axis
+#pragma unroll
+  for (int rr = 0; rr < RC; ++rr) {
+    int q, i1, i0;
+    unsigned off;
+    if (line(rr * NT + tid, q, i1, i0, off)) {
+      T r[m];
+      apply_st<T, K>(v[rr], r);
+      const int o = lds_base(D == 3 ? i1 * L::SI1 + q * mm + i0 : i0 * L::T0 + q * m);
+#pragma unroll
+      for (int a = 0; a < m; ++a) smem[o + a * (D == 3 ? m : 1)] = r[a];
+    }
+  }
+  __syncthreads();
+  if constexpr (D == 3) {
+    // ---- S^T along x1: lines (q, a2, i0)
+    T* W5 = smem + L::A;
+#pragma unroll
+    for (int rr = 0; rr < RC; ++rr) {
+      const int t = rr * NT + tid;
+      if (t < NB) {
+        T in[m], r[m];
+#pragma unroll
+        for (int i = 0; i < m; ++i) in[i] = smem[i * L::SI1 + t];
+        apply_st<T, K>(in, r);
+        const int g = div_small<m>(t), i0 = t - g * m;
+        const int o = lds_base(i0 * L::SI0 + g * m);
+#pragma unroll
+        for (int a = 0; a < m; ++a) W5[o + a] = r[a];
+      }
+    }
+    __syncthreads();
+  }
+  // ---- S^T along x0, 1 / (sum of eigenvalues), S along x0: lines (q, a2, a1) / (q, a1)
+  if constexpr (!kEarly) fetch_inv();
+  {
+    const T* in0 = D == 3 ? smem + L::A : smem;
+    T* out0 = D == 3 ? smem : smem + L::A;
+#pragma unroll
+    for (int rr = 0; rr < RC; ++rr) {
+      const int t = rr * NT + tid;
+      if (t < NB) {
+        T in[m], z[m], w[m];
+#pragma unroll
+        for (int i = 0; i < m; ++i) in[i] = in0[i * (D == 3 ? L::SI0 : L::T0) + t];
+        apply_st<T, K>(in, z);
+#pragma unroll
+        for (int a = 0; a < m; ++a) z[a] *= iv[rr][a];
+        apply_s<T, K>(z, w);
+        int o;
+        if constexpr (D == 3) {
+          const int q = div_small<mm>(t), r = t - q * mm, a2 = div_small<m>(r), a1 = r - a2 * m;
+          o = lds_base(a1 * L::SA1 + q * mm + a2 * m);
+        } else {
+          const int q = div_small<m>(t), a1 = t - q * m;
+          o = lds_base(a1 * L::T0 + q * m);
+        }
+#pragma unroll
+        for (int i = 0; i < m; ++i) out0[o + i] = w[i];
+      }
+    }
+  }
+  __syncthreads();
+  if constexpr (D == 3) {
+    // ---- S along x1: lines (q, a2, i0)
+    T* W7 = smem + L::A;
+#pragma unroll
+    for (int rr = 0; rr < RC; ++rr) {
+      const int t = rr * NT + tid;
+      if (t < NB) {
+        T in[m], w[m];
+#pragma unroll
+        for (int a = 0; a < m; ++a) in[a] = smem[a * L::SA1 + t];
+        apply_s<T, K>(in, w);
+        const int q = div_small<mm>(t), r = t - q * mm, a2 = div_small<m>(r), i0 = r - a2 * m;
+        const int o = lds_base(a2 * L::SA2 + q * m + i0);
+#pragma unroll
+        for (int i = 0; i < m; ++i) W7[o + i * (PPW * m)] = w[i];
+      }
+    }
+    __syncthreads();
+  }
+  // ---- S along the slowest axis, straight to global
+#pragma unroll
+  for (int rr = 0; rr < RC; ++rr) {
+    const int t = rr * NT + tid;
+    int q, i1, i0;
+    unsigned off;
+    if (line(t, q, i1, i0, off)) {
+      T in[m], w[m];
+#pragma unroll
+      for (int a = 0; a < m; ++a) in[a] = smem[L::A + a * (D == 3 ? L::SA2 : L::T0) + t];
+      apply_s<T, K>(in, w);
+#pragma unroll
+      for (int i = 0; i < m; ++i) xw.store(pl[i], off, ZERO ? sol_scale * w[i] : fma(sol_scale, w[i], xo[rr][i]));
+    }
+  }
+}
+
+// Launch shapes of these passes, as EigShapes (no shared layout): the fastest of 4-6 per row.  Measured, additive step
+// per pass, us, against the closure-free lines form they replace (one node line order, two patches per workgroup in 3D
+// Q4): 3D degree 4 64^3 cells FP32 29.4 (39.3), FP64 56.3 (59.9); degree 3 64^3 FP32 12.7 (21.2); degree 5 32^3 FP32
+// 9.9 (14.1); first colour from zero, 3D Q4 64^3 FP32 26.8.
+template <int D, int K, typename T>
+struct AddShapes {
+  static constexpr int PPW = D == 3 ? (K == 1 ? 64 : K == 2 ? 16 : K == 3 ? 8 : K == 4 ? 4 : K <= 6 ? 2 : 1)
+                                    : (K == 1 ? 64 : K == 2 ? 42 : K == 3 ? 12 : K == 4 ? 16 : K == 5 ? 7 : K == 6 ? 5 : 4);
+  static constexpr int NT = D == 3 ? (K == 1 ? 64 : K == 2 || K == 5 ? 192 : 256) : (K == 2 || K == 4 ? 128 : 64);
+  using Large = EigShape<PPW, NT, false>;
+  using Small = EigShape<(D == 3 ? (K == 1 ? 16 : K == 2 ? 4 : K == 3 ? 2 : 1) : (K == 1 ? 16 : K <= 4 ? 8 : 4)),
+                         (D == 3 ? (K <= 3 ? 64 : K == 7 ? 192 : 128) : 64), false>;
+};
+
 // ------------------------------------------------------------------ residual form
 
 // LDS of the 3D multiplicative pass below (T words).  Buffer A holds PM, PA [i2][j1][c], later the
@@ -1378,7 +1604,7 @@ __device__ __forceinline__ void colour_pass_mult3(T* __restrict__ smem, const T*
   }
 }
 
-// Wide shape of the 3D Q4 FP32 colour pass (residual form, and the first colour from zero): five patches per workgroup on 256 threads.  Its 49-line stages fill 245 of 256 lanes,
+// Wide shape of the 3D Q4 FP32 colour pass (residual form): five patches per workgroup on 256 threads.  Its 49-line stages fill 245 of 256 lanes,
 // against 98 of 128 for the two-patch default, which cuts the vector instructions per patch by
 // about a fifth.  A row of patches along x0 that is not a multiple of five leaves a partial
 // workgroup, so launches take it only on long rows (at most kWideIdle idle patch slots per row, as a
@@ -1388,7 +1614,7 @@ constexpr double kWideIdle = 0.15;
 template <int D, int K, typename T, int MODE>
 struct HasWideForm {
   static constexpr bool value = D == 3 && K == 4 && sizeof(T) == 4 &&
-                                (MODE == kModeResidual || MODE == kModeZero);
+                                MODE == kModeResidual;
 };
 template <int D, int K, typename T, int MODE, int PPW>
 struct IsWide {
@@ -1422,12 +1648,9 @@ __device__ __forceinline__ void colour_pass_lines(T* __restrict__ smem, const T*
                                                   int groups0, T res_scale, T sol_scale, unsigned blk) {
   constexpr int n = 2 * K + 1, m = 2 * K - 1, mm = m * m;
   constexpr int NT = IsWide<D, K, T, MODE, PPW>::value ? kWideNT : SmootherShape<D, K>::NT;
-  // ZERO: the additive pass on x = 0 that also writes the zeros of the rest of its closures
-  constexpr bool ZERO = MODE == kModeZero;
-  constexpr bool ADD = MODE == kModeAdditive || ZERO;
   // patch matrices and eigenvectors as compile-time constants (instruction literals / SGPR moves)
   using PT = gen::PatchTables<T, K>;
-  using L = SmootherLds<D, K, T, ADD, PPW, LinesAlias<D, K, T, MODE, PPW>::value, LinesPair<D, K, T, MODE, PPW>::value>;
+  using L = SmootherLds<D, K, T, PPW, LinesAlias<D, K, T, MODE, PPW>::value, LinesPair<D, K, T, MODE, PPW>::value>;
   constexpr int RS = L::RS;
   (void)p2;
 
@@ -1447,7 +1670,7 @@ __device__ __forceinline__ void colour_pass_lines(T* __restrict__ smem, const T*
   // Lines along the slowest axis, task = (q, i1, i0) in 3D / (q, i0) in 2D with i0 fastest:
   // the residual stage reads b on them and the last stage updates x^I on them.  b is
   // prefetched now (clamped to a valid patch so the loads are always in bounds); the old x^I
-  // comes from the closure in LDS in multiplicative mode and from global memory in additive mode.
+  // comes from the closure in LDS.
   constexpr int NB = D == 3 ? PPW * mm : PPW * m;
   constexpr int RB = (NB + NT - 1) / NT;
   T bpre[RB][m], xpre[RB][m];
@@ -1474,61 +1697,12 @@ __device__ __forceinline__ void colour_pass_lines(T* __restrict__ smem, const T*
     const int st = D == 3 ? ld2 : ld1;
 #pragma unroll
     for (int i = 0; i < m; ++i) bpre[rr][i] = ld_lane(bo + st + i * st, loff[rr]);
-    if constexpr (ADD && !ZERO) {
-#pragma unroll
-      for (int i = 0; i < m; ++i) xpre[rr][i] = ld_lane(xo + st + i * st, loff[rr]);
-    }
-    if constexpr (ZERO) {
-#pragma unroll
-      for (int i = 0; i < m; ++i) xpre[rr][i] = T(0);
-    }
-  }
-
-  if constexpr (ZERO) {
-    // 0 on every closure node of the workgroup that is not a patch interior (neighbouring
-    // workgroups write the same zeros on shared faces; no interior of the colour lies there).
-    // Those nodes are the closure rows on its faces, whole, and on the other rows the columns
-    // between patches (every 2k-th); rows run along x0.
-    constexpr int NFR = D == 3 ? 4 * (n - 1) : 2;  // face rows (j2, j1) / (j1)
-    constexpr int NIR = D == 3 ? m * m : m;        // other rows
-    constexpr int NZF = NFR * RS, NZ = NZF + NIR * (PPW + 1);
-    for (int w = tid; w < NZ; w += NT) {
-      int j1, j2 = 0, c;
-      if (w < NZF) {
-        const int f = w / RS;
-        c = w - f * RS;
-        if constexpr (D == 3) {
-          if (f < n) {
-            j2 = 0;
-            j1 = f;
-          } else if (f < 2 * n) {
-            j2 = n - 1;
-            j1 = f - n;
-          } else {
-            j2 = 1 + (f - 2 * n) / 2;
-            j1 = (f & 1) ? n - 1 : 0;  // f - 2n and f have the same parity (2n even)
-          }
-        } else {
-          j1 = f == 0 ? 0 : n - 1;
-        }
-      } else {
-        const int v = w - NZF, r = v / (PPW + 1);
-        c = 2 * K * (v - r * (PPW + 1));
-        if constexpr (D == 3) {
-          j2 = 1 + r / m;
-          j1 = 1 + (r - (r / m) * m);
-        } else {
-          j1 = 1 + r;
-        }
-      }
-      if (c < seg) st_lane(xo, (unsigned)((D == 3 ? j2 * ld2 : 0) + j1 * ld1 + c) * (unsigned)sizeof(T), T(0));
-    }
   }
 
   // ---- closure segment -> LDS X [j2][j1][c].  Work item = (column c, row j1 in 3D); the
   // slowest axis is walked unrolled.  Every closure node lies inside the grid: loads are
   // unconditional and Dirichlet nodes are replaced by 0 (boundary entries of x are ignored).
-  if constexpr (!ADD) {
+  {
     T* X = smem + (D == 3 ? L::offX : L::offX2);
     constexpr int NW = D == 3 ? RS * n : RS;
     const bool lo1 = s1 == 0, hi1 = s1 + n - 1 == n1d - 1;
@@ -1564,7 +1738,7 @@ __device__ __forceinline__ void colour_pass_lines(T* __restrict__ smem, const T*
 
   if constexpr (D == 3) {
     constexpr int SJ1 = L::SJ1, SJ2 = L::SJ2, SI1 = L::SI1, SI0 = L::SI0, SA1 = L::SA1, SA2 = L::SA2;
-    if constexpr (!ADD) {
+    {
       const T* X = smem + L::offX;
       T* PM = smem + L::offP;  // [j1][q][j2][i0]
       T* PA = PM + n * SJ1;
@@ -1743,10 +1917,7 @@ __device__ __forceinline__ void colour_pass_lines(T* __restrict__ smem, const T*
       const int i1 = r / m, i0 = r - i1 * m;
       if (task < NB && q < P) {
         T res[m];
-        if constexpr (ADD) {
-#pragma unroll
-          for (int i = 0; i < m; ++i) res[i] = bpre[rr][i];
-        } else {
+        {
           const T* U = smem + L::offUV;
           const T* V = U + n * SJ2;
           T u[n], v[n];
@@ -1867,7 +2038,7 @@ __device__ __forceinline__ void colour_pass_lines(T* __restrict__ smem, const T*
   } else {
     // ================================ 2D =====================================
     constexpr int T1 = L::T1, T0 = L::T0, TA = L::TA;
-    if constexpr (!ADD) {
+    {
       const T* X = smem + L::offX2;
       T* PM = smem + L::offP2;  // [j1][q][i0]
       T* PA = PM + n * T1;
@@ -1938,7 +2109,7 @@ __device__ __forceinline__ void colour_pass_lines(T* __restrict__ smem, const T*
       }
       __syncthreads();
     }
-    // ---- residual along x1, r = b - (A1 (M0 x) + M1 (A0 x)) (or r = b), then Sᵀ along x1:
+    // ---- residual along x1, r = b - (A1 (M0 x) + M1 (A0 x)) , then Sᵀ along x1:
     //      lines (q, i0), i0 fastest.  Aliased layout: W overwrites PM/PA, so every line is
     //      computed before the workgroup synchronises and writes.
     T* W = smem + L::offW;  // [i0][q][a1]
@@ -1949,10 +2120,7 @@ __device__ __forceinline__ void colour_pass_lines(T* __restrict__ smem, const T*
       const int q = task / m;
       if (task < NB && q < P) {
         T res[m];
-        if constexpr (ADD) {
-#pragma unroll
-          for (int i = 0; i < m; ++i) res[i] = bpre[rr][i];
-        } else {
+        {
           const T* PM = smem + L::offP2;
           const T* PA = PM + n * T1;
           T pm[n], pa[n];
@@ -2061,7 +2229,7 @@ struct MfmaLds {
   static constexpr int P = 2 * m * LS0;            // PM, PA
   static constexpr int UV = 2 * m * LS1;           // U, V
   static constexpr int Q = m * LS2;                // A2 U + M2 V
-  using Fd = SmootherLds<3, K, float, false, PPW>;  // strides of the diagonalisation stages
+  using Fd = SmootherLds<3, K, float, PPW>;  // strides of the diagonalisation stages
   static constexpr int FD = m * (Fd::SI1 > Fd::SI0 ? (Fd::SI1 > Fd::SA1 ? (Fd::SI1 > Fd::SA2 ? Fd::SI1 : Fd::SA2)
                                                                          : (Fd::SA1 > Fd::SA2 ? Fd::SA1 : Fd::SA2))
                                                    : (Fd::SI0 > Fd::SA1 ? (Fd::SI0 > Fd::SA2 ? Fd::SI0 : Fd::SA2)
@@ -2353,10 +2521,11 @@ template <int D, int K, typename T, int MODE, typename SH>
 struct ColourBody {
   // the residual form of the 3D pass in FP64 contracts the closure along x2 first, where it measured 3-9%
   // faster than the closure-through-LDS form; in FP32 the two measured within 2%
-  static constexpr bool kMult3 = D == 3 && MODE == kModeResidual && sizeof(T) == 8;
+  static_assert(MODE == kModeResidual, "line shapes serve the residual form");
+  static constexpr bool kMult3 = D == 3 && sizeof(T) == 8;
   static constexpr int lds() {
     if constexpr (kMult3) return Mult3Lds<K, SH::PPW>::total;
-    else return SmootherLds<D, K, T, MODE != kModeResidual, SH::PPW, LinesAlias<D, K, T, MODE, SH::PPW>::value,
+    else return SmootherLds<D, K, T, SH::PPW, LinesAlias<D, K, T, MODE, SH::PPW>::value,
                             LinesPair<D, K, T, MODE, SH::PPW>::value>::total;
   }
   static constexpr int kLds = lds();
@@ -2378,21 +2547,48 @@ struct ColourBody<D, K, T, MODE, EigShape<PPW, NT, AL>> {
     else return EigLds2<K, SH>::total;
   }
   static constexpr int kLds = lds();
-  static __device__ __forceinline__ void run(T* smem, const T* b, T* x, long long n1d, int p0, int p1, int p2, int cnt0,
-                                             int cnt1, int groups0, T, T sol_scale, unsigned blk) {
+  static __device__ __forceinline__ void run_team(T* smem, int tid, bool active, const T* b, T* x, long long n1d, int p0,
+                                                  int p1, int p2, int cnt0, int cnt1, int groups0, T, T sol_scale,
+                                                  unsigned blk) {
     if constexpr (D == 3)
-      colour_pass_eig3<K, T, kPoison, SH>(smem, b, x, n1d, p0, p1, p2, cnt0, cnt1, groups0, sol_scale, blk);
+      colour_pass_eig3<K, T, kPoison, SH>(smem, b, x, n1d, p0, p1, p2, cnt0, cnt1, groups0, sol_scale, blk, tid, active);
     else
-      colour_pass_eig2<K, T, kPoison, SH>(smem, b, x, n1d, p0, p1, cnt0, cnt1, groups0, sol_scale, blk);
+      colour_pass_eig2<K, T, kPoison, SH>(smem, b, x, n1d, p0, p1, cnt0, cnt1, groups0, sol_scale, blk, tid, active);
+  }
+  static __device__ __forceinline__ void run(T* smem, const T* b, T* x, long long n1d, int p0, int p1, int p2, int cnt0,
+                                             int cnt1, int groups0, T res_scale, T sol_scale, unsigned blk) {
+    run_team(smem, threadIdx.x, true, b, x, n1d, p0, p1, p2, cnt0, cnt1, groups0, res_scale, sol_scale, blk);
   }
 };
+template <int D, int K, typename T, bool ZERO, typename SH>
+struct AddBody {
+  static constexpr int kLds = AddLds<D, K, SH>::total;
+  static __device__ __forceinline__ void run_team(T* smem, int tid, bool active, const T* b, T* x, long long n1d, int p0,
+                                                  int p1, int p2, int cnt0, int cnt1, int groups0, T, T sol_scale,
+                                                  unsigned blk) {
+    colour_pass_add<D, K, T, ZERO, SH>(smem, b, x, n1d, p0, p1, p2, cnt0, cnt1, groups0, sol_scale, blk, tid, active);
+  }
+  static __device__ __forceinline__ void run(T* smem, const T* b, T* x, long long n1d, int p0, int p1, int p2, int cnt0,
+                                             int cnt1, int groups0, T res_scale, T sol_scale, unsigned blk) {
+    run_team(smem, threadIdx.x, true, b, x, n1d, p0, p1, p2, cnt0, cnt1, groups0, res_scale, sol_scale, blk);
+  }
+};
+template <int D, int K, typename T, int PPW, int NT, bool AL>
+struct ColourBody<D, K, T, kModeAdditive, EigShape<PPW, NT, AL>> : AddBody<D, K, T, false, EigShape<PPW, NT, AL>> {};
+template <int D, int K, typename T, int PPW, int NT, bool AL>
+struct ColourBody<D, K, T, kModeZero, EigShape<PPW, NT, AL>> : AddBody<D, K, T, true, EigShape<PPW, NT, AL>> {};
 template <int D, typename T, int MODE, int PPW>
 struct ColourBody<D, 1, T, MODE, Q1Shape<PPW>> {
   static constexpr int kLds = 1;
-  static __device__ __forceinline__ void run(T*, const T* b, T* x, long long n1d, int p0, int p1, int p2, int cnt0,
-                                             int cnt1, int groups0, T res_scale, T sol_scale, unsigned blk) {
+  static __device__ __forceinline__ void run_team(T*, int tid, bool active, const T* b, T* x, long long n1d, int p0, int p1,
+                                                  int p2, int cnt0, int cnt1, int groups0, T res_scale, T sol_scale,
+                                                  unsigned blk) {
     colour_pass_q1<D, T, MODE == kModeMultiplicative, PPW>(b, x, n1d, p0, p1, p2, cnt0, cnt1, groups0, res_scale,
-                                                           sol_scale, blk);
+                                                           sol_scale, blk, tid, active);
+  }
+  static __device__ __forceinline__ void run(T* smem, const T* b, T* x, long long n1d, int p0, int p1, int p2, int cnt0,
+                                             int cnt1, int groups0, T res_scale, T sol_scale, unsigned blk) {
+    run_team(smem, threadIdx.x, true, b, x, n1d, p0, p1, p2, cnt0, cnt1, groups0, res_scale, sol_scale, blk);
   }
 };
 template <int D, int K, int PPW, int NT>
@@ -2427,6 +2623,156 @@ __global__ __launch_bounds__((SH::NT)) void colour_pass_group_kernel(ColourPassG
   const ColourPassDesc& d = grp.e[e];
   Body::run(smem, (const T*)d.b, (T*)d.x, d.n1d, d.p[0], d.p[1], d.p[2], d.cnt0, d.cnt1, d.groups0, (T)d.res_scale,
             (T)d.sol_scale, g - (unsigned)d.block_begin);
+}
+
+// ------------------------------------------------------------------ several colours in one launch
+//
+// Small levels are bound by launches: a pass takes 2.5-3 us from one kernel's end to the next one's start and
+// 1-2 us of work.  The colours that differ in the parity of x0 only (c and c ^ 1) touch a row of patches along
+// x0 independently of all other rows: the closures of a row's patches span the same x1 and x2 range, and the
+// nodes that the two colours update lie strictly inside it.  So one workgroup can run both colours of a row, one
+// after the other, without any synchronisation between workgroups; likewise four colours (x0 and x1 parities) of
+// a layer of patches in 3D, and all colours of the whole grid.  Span 1, 2, 3: row, layer, grid (2D: 1 row,
+// 2 grid).  The workgroup's teams of threads take the row's (layer's, grid's) blocks of patches in turn.
+// A pass here is the eigenbasis form without a look at old interior values, so it serves corrections; ADD: the
+// additive pass.
+template <int D, int K, typename T>
+struct FusedTeams;  // SH: a team's shape; N: teams per workgroup
+template <typename T> struct FusedTeams<3, 1, T> { using SH = Q1Shape<64>; static constexpr int N = 8; };
+template <typename T> struct FusedTeams<3, 2, T> { using SH = EigShape<4, 128, false>; static constexpr int N = 4; };
+template <typename T> struct FusedTeams<3, 3, T> { using SH = EigShape<2, 128, false>; static constexpr int N = 4; };
+template <typename T> struct FusedTeams<3, 4, T> { using SH = EigShape<2, 128, false>; static constexpr int N = 4; };
+template <typename T> struct FusedTeams<3, 5, T> { using SH = EigShape<1, 128, false>; static constexpr int N = 4; };
+template <typename T> struct FusedTeams<3, 6, T> { using SH = EigShape<1, 192, true>; static constexpr int N = 4; };
+template <typename T> struct FusedTeams<3, 7, T> { using SH = EigShape<1, 256, true>; static constexpr int N = 4; };
+template <typename T> struct FusedTeams<2, 1, T> { using SH = Q1Shape<64>; static constexpr int N = 8; };
+template <typename T> struct FusedTeams<2, 2, T> { using SH = EigShape<8, 64, false>; static constexpr int N = 8; };
+template <typename T> struct FusedTeams<2, 3, T> { using SH = EigShape<4, 64, false>; static constexpr int N = 8; };
+template <typename T> struct FusedTeams<2, 4, T> { using SH = EigShape<4, 128, false>; static constexpr int N = 8; };
+template <typename T> struct FusedTeams<2, 5, T> { using SH = EigShape<4, 128, false>; static constexpr int N = 8; };
+template <typename T> struct FusedTeams<2, 6, T> { using SH = EigShape<4, 128, false>; static constexpr int N = 8; };
+template <typename T> struct FusedTeams<2, 7, T> { using SH = EigShape<4, 128, false>; static constexpr int N = 8; };
+
+struct FusedMembers {
+  const void* b[kMaxGroup];
+  void* x[kMaxGroup];
+};
+
+template <int D, int K, typename T, bool ADD>
+__global__ __launch_bounds__((FusedTeams<D, K, T>::SH::NT * FusedTeams<D, K, T>::N)) void colour_span_kernel(
+    FusedMembers mem, long long n1d, int half, int span, int first, int n_colours, int step, int clear, T res_scale,
+    T sol_scale) {
+  using SH = typename FusedTeams<D, K, T>::SH;
+  using Body = std::conditional_t<ADD, AddBody<D, K, T, false, SH>,
+                                  ColourBody<D, K, T, K == 1 ? kModeMultiplicative : kModeBoundary, SH>>;
+  constexpr int TEAMS = FusedTeams<D, K, T>::N, NT = SH::NT, PPW = SH::PPW;
+  constexpr int kLds = (Body::kLds + 3) & ~3;
+  __shared__ __align__(16) T smem[kLds * TEAMS];
+  const int team = __builtin_amdgcn_readfirstlane((int)threadIdx.x / NT), tid = (int)threadIdx.x - team * NT;
+  const T* b = (const T*)mem.b[blockIdx.y];
+  T* x = (T*)mem.x[blockIdx.y];
+  const int w = blockIdx.x;
+  if (clear) {
+    // x holds anything: 0 on the closures of this workgroup's row, layer or grid.  Neighbouring workgroups write
+    // the same zeros on shared faces, and nobody updates those in this launch.
+    const int cnt = half;  // colour 0: half patches per axis
+    const long long nr1 = span == 1 ? 2 * K + 1 : n1d;
+    const int t1 = span == 1 ? w % cnt : 0, t2 = span == 1 ? w / cnt : w;
+    const long long o1 = span == 1 ? 2LL * K * t1 : 0;
+    const long long nr2 = D == 2 ? 1 : span == 3 ? n1d : 2 * K + 1, o2 = D == 2 || span == 3 ? 0 : 2LL * K * t2;
+    const long long rows = nr1 * nr2;
+    const int len = (int)n1d;
+    for (long long r = threadIdx.x >> 6; r < rows; r += blockDim.x >> 6) {
+      const long long j2 = r / nr1, j1 = r - j2 * nr1;
+      T* row = x + ((o2 + j2) * n1d * (D == 3 ? 1 : 0) + o1 + j1) * n1d;
+      for (int i = threadIdx.x & 63; i < len; i += 64) row[i] = T(0);
+    }
+    __syncthreads();
+  }
+  for (int ci = 0; ci < n_colours; ++ci) {
+    const int c = first + ci * step;
+    const int p0 = c & 1, p1 = (c >> 1) & 1, p2 = (c >> 2) & 1;
+    const int cnt0 = half - p0, cnt1 = half - p1, cnt2 = D == 3 ? half - p2 : 1;
+    const int groups0 = (cnt0 + PPW - 1) / PPW;
+    const int per = groups0 * (span >= 2 ? cnt1 : 1) * (span >= 3 ? cnt2 : 1);
+    for (int base = 0; base < per; base += TEAMS) {
+      const int k = base + team;
+      Body::run_team(smem + team * kLds, tid, k < per, b, x, n1d, p0, p1, p2, cnt0, cnt1, groups0, res_scale,
+                     sol_scale, (unsigned)(w * per + (k < per ? k : 0)));
+      __syncthreads();
+    }
+  }
+}
+
+// The exact solve on the coarsest level: one patch, FP64 arithmetic for both precisions, one workgroup per
+// member; the boundary nodes of x become 0.  Lines as in the passes above: S^T along x2, x1 and x0, the
+// eigenvalue scaling, S along x0, x1 and x2 (2D: x1, x0, x0, x1).
+template <int D, int K, typename T>
+__global__ __launch_bounds__(256) void coarse_solve_kernel(FusedMembers mem) {
+  constexpr int n = 2 * K + 1, m = 2 * K - 1, mm = m * m, L = D == 3 ? mm : m;
+  __shared__ double w0[L * m], w1[L * m];
+  const T* b = (const T*)mem.b[blockIdx.x];
+  T* x = (T*)mem.x[blockIdx.x];
+  const int t = threadIdx.x;
+  const DevTables<double>& tb = tab<double>(K);
+  for (int i = t; i < (D == 3 ? n * n * n : n * n); i += 256) {
+    const int i0 = i % n, i1 = (i / n) % n, i2 = i / (n * n);
+    if (i0 == 0 || i0 == n - 1 || i1 == 0 || i1 == n - 1 || (D == 3 && (i2 == 0 || i2 == n - 1))) x[i] = T(0);
+  }
+  // line t of the slowest axis: node (1 + i, 1 + t / m, 1 + t % m) in 3D, (1 + i, 1 + t) in 2D
+  const int base = D == 3 ? (1 + t / m) * n + 1 + t % m : 1 + t, st = D == 3 ? n * n : n;
+  double v[m], u[m];
+  if (t < L) {
+#pragma unroll
+    for (int i = 0; i < m; ++i) v[i] = (double)b[(1 + i) * st + base];
+    apply_st<double, K>(v, u);
+#pragma unroll
+    for (int a = 0; a < m; ++a) w0[a * L + t] = u[a];
+  }
+  __syncthreads();
+  if constexpr (D == 3) {
+    if (t < L) {
+      const int a2 = t / m, i0 = t % m;
+#pragma unroll
+      for (int i = 0; i < m; ++i) v[i] = w0[a2 * L + i * m + i0];
+      apply_st<double, K>(v, u);
+#pragma unroll
+      for (int a = 0; a < m; ++a) w1[a2 * L + a * m + i0] = u[a];
+    }
+    __syncthreads();
+  }
+  if (t < L) {
+    const double* in = D == 3 ? w1 : w0;  // lines (a2, a1) / a1 along x0
+    double* out = D == 3 ? w0 : w1;
+#pragma unroll
+    for (int i = 0; i < m; ++i) v[i] = in[t * m + i];
+    apply_st<double, K>(v, u);
+#pragma unroll
+    for (int a = 0; a < m; ++a) u[a] *= D == 3 ? tb.inv3[t * m + a] : tb.inv2[t * m + a];
+    apply_s<double, K>(u, v);
+#pragma unroll
+    for (int i = 0; i < m; ++i) out[t * m + i] = v[i];
+  }
+  __syncthreads();
+  if constexpr (D == 3) {
+    if (t < L) {
+      const int a2 = t / m, i0 = t % m;
+#pragma unroll
+      for (int a = 0; a < m; ++a) v[a] = w0[a2 * L + a * m + i0];
+      apply_s<double, K>(v, u);
+#pragma unroll
+      for (int i = 0; i < m; ++i) w1[a2 * L + i * m + i0] = u[i];
+    }
+    __syncthreads();
+  }
+  if (t < L) {
+    constexpr double scale = D == 3 ? 2.0 : 1.0;  // h^(2-d), h = 1/2
+#pragma unroll
+    for (int a = 0; a < m; ++a) v[a] = w1[a * L + t];
+    apply_s<double, K>(v, u);
+#pragma unroll
+    for (int i = 0; i < m; ++i) x[(1 + i) * st + base] = (T)(scale * u[i]);
+  }
 }
 
 // ------------------------------------------------------------------ host side
@@ -2482,6 +2828,14 @@ struct ModeShapes<D, K, T, kModeMultiplicative> {
 };
 template <int D, int K, typename T>
 struct ModeShapes<D, K, T, kModeBoundary> : ModeShapes<D, K, T, kModeMultiplicative> {};
+template <int D, int K, typename T>
+struct ModeShapes<D, K, T, kModeAdditive> {
+  using Large = typename AddShapes<D, K, T>::Large;
+  using Small = typename AddShapes<D, K, T>::Small;
+  static constexpr long long kMinBlocks = kEigWaves * 64 / Large::NT;
+};
+template <int D, int K, typename T>
+struct ModeShapes<D, K, T, kModeZero> : ModeShapes<D, K, T, kModeAdditive> {};
 using WideShape = LineShape<kWidePPW, kWideNT>;
 using MfmaShape = LineShape<kMfmaPPW, 256>;
 
@@ -2714,6 +3068,124 @@ hipError_t launch_colour_pass_group(int dim, int k, int prec, int mode, int colo
                   : group_k<3>(k, prec, mode, colour, members, n_members, st);
 }
 
+template <int D, int K, typename T, bool ADD>
+static hipError_t smooth_fused(const LevelGeom& g, int span, bool reverse, bool clear, const ColourPassMember* mem, int nm,
+                               hipStream_t st) {
+  using FT = FusedTeams<D, K, T>;
+  const int half = (int)(g.ncells / 2), top = D;  // span `top`: the whole grid
+  const int colours = 1 << span, sets = (1 << D) / colours;
+  const T res_scale = (T)(D == 3 ? g.h : 1.0), sol_scale = (T)(D == 3 ? 1.0 / g.h : 1.0);
+  for (int i0 = 0; i0 < nm; i0 += kMaxGroup) {
+    const int n = nm - i0 < kMaxGroup ? nm - i0 : kMaxGroup;
+    FusedMembers fm{};
+    for (int i = 0; i < n; ++i) {
+      fm.b[i] = mem[i0 + i].b;
+      fm.x[i] = mem[i0 + i].x;
+    }
+    for (int j = 0; j < sets; ++j) {
+      const int set = reverse ? sets - 1 - j : j;
+      const int first = set * colours + (reverse ? colours - 1 : 0);
+      int units = 1;  // workgroups: rows, layers, or the grid
+      for (int a = span; a < top; ++a) units *= half - ((first >> a) & 1);
+      hipLaunchKernelGGL((colour_span_kernel<D, K, T, ADD>), dim3(units, n), dim3(FT::SH::NT * FT::N), 0, st, fm, g.n1d, half,
+                         span, first, colours, reverse ? -1 : 1, clear && j == 0 ? 1 : 0, res_scale, sol_scale);
+      hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    }
+  }
+  return hipSuccess;
+}
+
+template <int D, int K, typename T>
+static hipError_t coarse_fused(const ColourPassMember* mem, int nm, hipStream_t st) {
+  for (int i0 = 0; i0 < nm; i0 += kMaxGroup) {
+    const int n = nm - i0 < kMaxGroup ? nm - i0 : kMaxGroup;
+    FusedMembers fm{};
+    for (int i = 0; i < n; ++i) {
+      fm.b[i] = mem[i0 + i].b;
+      fm.x[i] = mem[i0 + i].x;
+    }
+    hipLaunchKernelGGL((coarse_solve_kernel<D, K, T>), dim3(n), dim3(256), 0, st, fm);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+// Calls f.template operator()<D, K>() for the run-time (dim, degree).
+template <typename F>
+static hipError_t with_degree(int dim, int k, F f) {
+  switch (dim * 10 + k) {
+    case 21: return f(std::integral_constant<int, 2>{}, std::integral_constant<int, 1>{});
+    case 22: return f(std::integral_constant<int, 2>{}, std::integral_constant<int, 2>{});
+    case 23: return f(std::integral_constant<int, 2>{}, std::integral_constant<int, 3>{});
+    case 24: return f(std::integral_constant<int, 2>{}, std::integral_constant<int, 4>{});
+    case 25: return f(std::integral_constant<int, 2>{}, std::integral_constant<int, 5>{});
+    case 26: return f(std::integral_constant<int, 2>{}, std::integral_constant<int, 6>{});
+    case 27: return f(std::integral_constant<int, 2>{}, std::integral_constant<int, 7>{});
+    case 31: return f(std::integral_constant<int, 3>{}, std::integral_constant<int, 1>{});
+    case 32: return f(std::integral_constant<int, 3>{}, std::integral_constant<int, 2>{});
+    case 33: return f(std::integral_constant<int, 3>{}, std::integral_constant<int, 3>{});
+    case 34: return f(std::integral_constant<int, 3>{}, std::integral_constant<int, 4>{});
+    case 35: return f(std::integral_constant<int, 3>{}, std::integral_constant<int, 5>{});
+    case 36: return f(std::integral_constant<int, 3>{}, std::integral_constant<int, 6>{});
+    case 37: return f(std::integral_constant<int, 3>{}, std::integral_constant<int, 7>{});
+  }
+  return hipErrorInvalidValue;
+}
+
+// Spans from level 2 up, [dim - 2][k - 1][prec], where a fused step takes less device time than its single passes,
+// or up to 10% more (it also saves the host 2.4 us per launch).  One step, us, single passes against fused, FP32 /
+// FP64: 3D degree 1 levels 2-4 17-20 / 18-22 against 10-15; degree 2 22, 25, 25 against 19, 24, 26; degree 3 30, 31,
+// 31 against 23, 29, 34; degree 4 level 2 32 / 38 against 28 / 39, level 4 36 / 44 against 43 / 58 (not taken: a
+// workgroup runs on one compute unit, and four teams saturate its vector units); degree 7 level 2 47 / 66 against
+// 62 / 129.  2D degree 1 levels 2-6 6.6-9.5 against 3.4-5.8; degree 4 level 3 12 / 15 against 9.5 / 14, level 5
+// 13.9 / 15.6 against 11.9 / 16.8; degree 7 level 3 16 / 22 against 14 / 21, level 5 FP64 23 against 28.
+static const char* const kFusedSpans[2][7][2] = {
+    {{"222111", "222111"},  // 2D; {FP64, FP32}
+     {"222111", "222111"},
+     {"2211", "22111"},
+     {"2211", "2211"},
+     {"221", "2211"},
+     {"211", "2211"},
+     {"111", "2211"}},
+    {{"321", "321"},  // 3D
+     {"321", "321"},
+     {"31", "311"},
+     {"3", "31"},
+     {"", "3"},
+     {"", "1"},
+     {"", ""}}};
+
+// The additive step's teams hold more registers: in FP64 from 2D degree 5 up they run at 3.2-5.5 us per pass on levels
+// 2-4 against 2.9-4.6 of its single passes, in FP32 from degree 5 up on level 5 at 2.8-4.0 against 2.9-3.6.
+int fused_span(const LevelGeom& g, int prec, bool additive) {
+  if (additive && g.dim == 2 && g.k >= 5 && (prec == 0 || g.level > 4)) return 0;
+  const char* s = kFusedSpans[g.dim - 2][g.k - 1][prec];
+  for (int i = 2; *s; ++i, ++s)
+    if (i == g.level) return *s - '0';
+  return 0;
+}
+
+hipError_t launch_smooth_fused(const LevelGeom& g, int prec, bool additive, int span, bool reverse, bool clear,
+                               const ColourPassMember* mem, int nm, hipStream_t st) {
+  return with_degree(g.dim, g.k, [&](auto d, auto k) {
+    constexpr int D = decltype(d)::value, K = decltype(k)::value;
+    if (additive)
+      return prec == 0 ? smooth_fused<D, K, double, true>(g, span, reverse, clear, mem, nm, st)
+                       : smooth_fused<D, K, float, true>(g, span, reverse, clear, mem, nm, st);
+    return prec == 0 ? smooth_fused<D, K, double, false>(g, span, reverse, clear, mem, nm, st)
+                     : smooth_fused<D, K, float, false>(g, span, reverse, clear, mem, nm, st);
+  });
+}
+
+hipError_t launch_coarse_solve(int dim, int k, int prec, const ColourPassMember* mem, int nm, hipStream_t st) {
+  return with_degree(dim, k, [&](auto d, auto kk) {
+    constexpr int D = decltype(d)::value, K = decltype(kk)::value;
+    return prec == 0 ? coarse_fused<D, K, double>(mem, nm, st) : coarse_fused<D, K, float>(mem, nm, st);
+  });
+}
+
 // ------------------------------------------------------------ host-side launch geometry
 
 namespace {
@@ -2759,6 +3231,8 @@ bool colour_launches_ok(const LevelGeom& g, long long* nblk, std::string* why) {
     if (!colour_shape_ok<D, K, LatencyPPW<D, K>::value>(g, c, nblk, why)) return false;
     if constexpr (HasMfmaForm<D, K, float>::value)
       if (!colour_shape_ok<D, K, kMfmaPPW>(g, c, nblk, why)) return false;
+    if (!colour_shape_ok<D, K, AddShapes<D, K, float>::Large::PPW>(g, c, nblk, why)) return false;
+    if (!colour_shape_ok<D, K, AddShapes<D, K, float>::Small::PPW>(g, c, nblk, why)) return false;
     if (!colour_shape_ok<D, K, EigShapes<D, K, float>::Large::PPW>(g, c, nblk, why)) return false;
     if (!colour_shape_ok<D, K, EigShapes<D, K, float>::Small::PPW>(g, c, nblk, why)) return false;
     if (!colour_shape_ok<D, K, EigShapes<D, K, double>::Large::PPW>(g, c, nblk, why)) return false;
