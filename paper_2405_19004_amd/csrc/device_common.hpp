@@ -92,6 +92,22 @@ struct Window {
       __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, vo, so, 0);
     }
   }
+  // the offset of a Dirichlet node (z) or of an ordinary one
+  static __device__ __forceinline__ unsigned masked(bool z, unsigned off) { return z ? kOutside : off; }
+};
+
+// The same accesses to a level vector in LDS, whose Dirichlet entries are 0.
+template <typename T>
+struct LdsWindow {
+  T* p;
+  __device__ __forceinline__ LdsWindow(const T* base, unsigned) : p(const_cast<T*>(base)) {}
+  __device__ __forceinline__ T load(unsigned so, unsigned vo) const {
+    return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(p) + (so + vo));
+  }
+  __device__ __forceinline__ void store(unsigned so, unsigned vo, T v) const {
+    *reinterpret_cast<T*>(reinterpret_cast<char*>(p) + (so + vo)) = v;
+  }
+  static __device__ __forceinline__ unsigned masked(bool, unsigned off) { return off; }
 };
 
 // t / D for 0 <= t < 4096 by one 24-bit multiply and a shift (full rate; the compiler's general form

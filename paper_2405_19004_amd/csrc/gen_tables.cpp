@@ -56,7 +56,8 @@ int main() {
   }
   std::printf("// Cell tables of degree K in precision T: reference stiffness Ah and mass Mh ((K+1)^2),\n"
               "// prolongation P ((2K+1) x (K+1): phi_a at fine position q of a coarse cell), band rows of the\n"
-              "// assembled 1D stiffness / mass (K x (2K+1)) and of the restriction (K x (4K+1)).\n");
+              "// assembled 1D stiffness / mass (K x (2K+1)) and of the restriction (K x (4K+1)); RA, RM = P^T times\n"
+              "// the stiffness / mass of a coarse cell's two fine cells ((K+1) x (2K+1)).\n");
   std::printf("template <typename T, int K>\nstruct CellTables;\n\n");
   for (int k = 1; k <= vps::kMaxDegree; ++k) {
     const vps::Tables1D& t = vps::tables_for_degree(k);
@@ -70,6 +71,22 @@ int main() {
       emit(type, "Ab", t.Aband, fmt);
       emit(type, "Mb", t.Mband, fmt);
       emit(type, "Rb", t.Rband, fmt);
+      const int np = k + 1, nf = 2 * k + 1;
+      for (int which = 0; which < 2; ++which) {
+        const std::vector<double>& cell = which ? t.Mhat : t.Ahat;
+        std::vector<double> R(np * nf);
+        for (int a = 0; a < np; ++a)
+          for (int j = 0; j < nf; ++j) {
+            long double v = 0;
+            for (int c = 0; c < 2; ++c) {
+              const int jj = j - c * k;
+              if (jj < 0 || jj > k) continue;
+              for (int i = 0; i < np; ++i) v += (long double)t.P[(c * k + i) * np + a] * cell[i * np + jj];
+            }
+            R[a * nf + j] = (double)v;
+          }
+        emit(type, which ? "RM" : "RA", R, fmt);
+      }
       std::printf("};\n\n");
     }
   }

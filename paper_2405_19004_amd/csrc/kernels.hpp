@@ -97,6 +97,11 @@ int fused_span(const LevelGeom& g, int prec, bool additive);
 // x = A_1^{-1} b on level 1 for every member, in FP64 arithmetic.
 hipError_t launch_coarse_solve(int dim, int k, int prec, const ColourPassMember* members, int n_members,
                                hipStream_t st);
+// x = V-cycle of b from x = 0 (multiplicative smoother; x holds anything on entry) on every member's level g.level,
+// in one launch; levels up to cycle_top(), which is 1 where there is no such form.
+int cycle_top(int dim, int k, int prec);
+hipError_t launch_cycle(int dim, int k, int prec, bool post_reverse, const ColourPassMember* members, int n_members,
+                        hipStream_t st);
 
 // smoother.hip
 hipError_t launch_colour_pass(const LevelGeom& g, int prec, int mode, int colour, const void* b, void* x,

@@ -249,28 +249,38 @@ Status coarse_solve(Problem* p, int prec, const void* b, void* x) {
   return Status::ok();
 }
 
+// The level up to which one launch runs a V-cycle on `top`: its iterate starts from 0 there.
+static int low_levels(const Problem* p, int prec, int top, bool top_zero) {
+  if (vcycle_mode(p) != kModeMultiplicative) return 1;
+  return std::max(1, std::min(cycle_top(p->dim, p->k, prec), top_zero ? top : top - 1));
+}
+
 Status vcycle_top(Problem* p, int prec, int top, const void* bT, void* xT, bool top_zero) {
   if (!p->has(prec)) return Status{-1, "V-cycle precision was not requested at creation"};
-  if (top == 1) return coarse_solve(p, prec, bT, xT);
   const bool post_rev = !p->post_same_order;
+  auto level_b = [&](int lvl) -> const void* { return lvl == top ? bT : p->lv[lvl].b[prec]; };
+  auto level_x = [&](int lvl) -> void* { return lvl == top ? xT : p->lv[lvl].x[prec]; };
+  const int low = low_levels(p, prec, top, top_zero);
   // descend
-  for (int lvl = top; lvl >= 2; --lvl) {
-    const void* b = lvl == top ? bT : p->lv[lvl].b[prec];
-    void* x = lvl == top ? xT : p->lv[lvl].x[prec];
+  for (int lvl = top; lvl > low; --lvl) {
     // below the top, x starts from 0 (the first pass writes every node)
     const bool zero = lvl < top || top_zero;
-    VPS_TRY(smoother(p, lvl, prec, vcycle_mode(p), false, b, x, zero, zero ? StepUse::kCorrection : StepUse::kStep));
-    VPS_HIP(launch_operator(p->geom(lvl), prec, x, b, p->lv[lvl].r[prec], p->stream));
+    VPS_TRY(smoother(p, lvl, prec, vcycle_mode(p), false, level_b(lvl), level_x(lvl), zero,
+                     zero ? StepUse::kCorrection : StepUse::kStep));
+    VPS_HIP(launch_operator(p->geom(lvl), prec, level_x(lvl), level_b(lvl), p->lv[lvl].r[prec], p->stream));
     VPS_HIP(launch_restrict(p->geom(lvl), prec, p->lv[lvl].r[prec], p->lv[lvl - 1].b[prec], p->lv[lvl].t[prec],
                             p->stream));
   }
-  VPS_TRY(coarse_solve(p, prec, p->lv[1].b[prec], p->lv[1].x[prec]));
+  if (low > 1) {
+    const ColourPassMember m{p->geom(low), level_b(low), level_x(low)};
+    VPS_HIP(launch_cycle(p->dim, p->k, prec, post_rev, &m, 1, p->stream));
+  } else {
+    VPS_TRY(coarse_solve(p, prec, level_b(1), level_x(1)));
+  }
   // ascend
-  for (int lvl = 2; lvl <= top; ++lvl) {
-    const void* b = lvl == top ? bT : p->lv[lvl].b[prec];
-    void* x = lvl == top ? xT : p->lv[lvl].x[prec];
-    VPS_HIP(launch_prolongate_add(p->geom(lvl), prec, p->lv[lvl - 1].x[prec], x, p->stream));
-    VPS_TRY(smoother(p, lvl, prec, vcycle_mode(p), post_rev, b, x, false,
+  for (int lvl = low + 1; lvl <= top; ++lvl) {
+    VPS_HIP(launch_prolongate_add(p->geom(lvl), prec, p->lv[lvl - 1].x[prec], level_x(lvl), p->stream));
+    VPS_TRY(smoother(p, lvl, prec, vcycle_mode(p), post_rev, level_b(lvl), level_x(lvl), false,
                      lvl < top || top_zero ? StepUse::kCorrection : StepUse::kLast));
   }
   return Status::ok();
@@ -363,7 +373,7 @@ Status fmg(Problem* p, int prec, const void* const* b_levels, void* x, double ep
   return Status::ok();
 }
 
-Status vcycle_group(Problem* const* ps, int n, int prec, const void* const* bL, void* const* xL, bool top_zero) {
+Status vcycle_group(Problem* const* ps, int n, int prec, const void* const* bL, void* const* xL) {
   if (n <= 0) return Status::ok();
   int Lmax = 0;
   for (int i = 0; i < n; ++i) {
@@ -379,13 +389,12 @@ Status vcycle_group(Problem* const* ps, int n, int prec, const void* const* bL, 
   auto level_b = [&](int i, int lvl) -> const void* { return lvl == ps[i]->L ? bL[i] : ps[i]->lv[lvl].b[prec]; };
   auto level_x = [&](int i, int lvl) -> void* { return lvl == ps[i]->L ? xL[i] : ps[i]->lv[lvl].x[prec]; };
   std::vector<ColourPassMember> mem, sep;
-  // x_zero: every member's x is 0 on entry (the first colour then needs no residual, as in smoother())
-  auto smooth = [&](int lvl, bool reverse, bool x_zero, bool post) -> Status {
+  // x_zero: every member's x counts as 0 on entry (the first colour then needs no residual, as in smoother())
+  auto smooth = [&](int lvl, bool reverse, bool x_zero) -> Status {
     mem.clear();
     for (int i = 0; i < n; ++i)
       if (ps[i]->L >= lvl) mem.push_back({ps[i]->geom(lvl), level_b(i, lvl), level_x(i, lvl)});
-    const StepUse use = top_zero ? StepUse::kCorrection : post ? StepUse::kLast : StepUse::kStep;
-    if (vcycle_mode(ps[0]) == kModeMultiplicative && use == StepUse::kCorrection) {
+    if (vcycle_mode(ps[0]) == kModeMultiplicative) {
       if (const int span = fused_span(mem[0].g, prec, false)) {
         VPS_HIP(launch_smooth_fused(mem[0].g, prec, false, span, reverse, x_zero, mem.data(), (int)mem.size(), st));
         return Status::ok();
@@ -393,7 +402,7 @@ Status vcycle_group(Problem* const* ps, int n, int prec, const void* const* bL, 
     }
     for (int j = 0; j < nc; ++j) {
       const int c = reverse ? nc - 1 - j : j;
-      const int mode = step_mode(vcycle_mode(ps[0]), mem[0].g, prec, j, c, reverse, x_zero, use);
+      const int mode = step_mode(vcycle_mode(ps[0]), mem[0].g, prec, j, c, reverse, x_zero, StepUse::kCorrection);
       if (mode == kSmoothSeparate) {
         // residual of every member, then the packed local solves on it
         sep.assign(mem.begin(), mem.end());
@@ -410,9 +419,9 @@ Status vcycle_group(Problem* const* ps, int n, int prec, const void* const* bL, 
     }
     return Status::ok();
   };
-  for (int lvl = Lmax; lvl >= 2; --lvl) {
-    // levels below a member's top start from 0 (the first pass writes every node)
-    VPS_TRY(smooth(lvl, false, top_zero, false));
+  const int low = low_levels(ps[0], prec, Lmax, true);
+  for (int lvl = Lmax; lvl > low; --lvl) {
+    VPS_TRY(smooth(lvl, false, true));
     for (int i = 0; i < n; ++i) {
       if (ps[i]->L < lvl) continue;
       Problem* p = ps[i];
@@ -421,13 +430,17 @@ Status vcycle_group(Problem* const* ps, int n, int prec, const void* const* bL, 
     }
   }
   mem.clear();
-  for (int i = 0; i < n; ++i) mem.push_back({ps[i]->geom(1), level_b(i, 1), level_x(i, 1)});
-  VPS_HIP(launch_coarse_solve(dim, k, prec, mem.data(), n, st));
-  for (int lvl = 2; lvl <= Lmax; ++lvl) {
+  for (int i = 0; i < n; ++i) {
+    const int l = std::min(low, ps[i]->L);
+    mem.push_back({ps[i]->geom(l), level_b(i, l), level_x(i, l)});
+  }
+  VPS_HIP(low > 1 ? launch_cycle(dim, k, prec, post_rev, mem.data(), n, st)
+                  : launch_coarse_solve(dim, k, prec, mem.data(), n, st));
+  for (int lvl = low + 1; lvl <= Lmax; ++lvl) {
     for (int i = 0; i < n; ++i)
       if (ps[i]->L >= lvl)
         VPS_HIP(launch_prolongate_add(ps[i]->geom(lvl), prec, ps[i]->lv[lvl - 1].x[prec], level_x(i, lvl), st));
-    VPS_TRY(smooth(lvl, post_rev, false, true));
+    VPS_TRY(smooth(lvl, post_rev, false));
   }
   return Status::ok();
 }
@@ -525,7 +538,7 @@ Status precondition_group(Problem* const* ps, int n, int mode) {
       xs[i] = B.x[1];
     }
   }
-  VPS_TRY(vcycle_group(ps, n, prec, bs.data(), xs.data(), true));
+  VPS_TRY(vcycle_group(ps, n, prec, bs.data(), xs.data()));
   for (int i = 0; i < n; ++i) {
     Problem* p = ps[i];
     const long long N = p->lv[p->L].N;

@@ -83,7 +83,7 @@ Status vcycle_top(Problem* p, int prec, int top, const void* b, void* x, bool to
 // V-cycles of n problems of the same (dim, degree), all on one stream, in lockstep: every colour
 // pass of a level is one packed launch over the problems that have that level.  Each problem's
 // arithmetic (and result) is exactly that of vcycle() on it alone.
-Status vcycle_group(Problem* const* ps, int n, int prec, const void* const* bL, void* const* xL, bool top_zero);
+Status vcycle_group(Problem* const* ps, int n, int prec, const void* const* bL, void* const* xL);
 
 struct SolveStats {
   int iterations = 0;

@@ -353,7 +353,7 @@ struct EigLds3 {
 // different blocks and meet at the barriers); active: whether the team has a block.
 // POISON: a non-finite old interior value makes the patch's result non-finite, as the residual form
 // does (x^I enters through one multiply-add by zero per node); without it x^I is never read.
-template <int K, typename T, bool POISON, typename SH>
+template <int K, typename T, bool POISON, typename SH, typename Win = Window<T>>
 __device__ __forceinline__ void colour_pass_eig3(T* __restrict__ smem, const T* __restrict__ b, T* __restrict__ x,
                                                  long long n1d, int p0, int p1, int p2, int cnt0, int cnt1,
                                                  int groups0, T sol_scale, unsigned blk, int tid, bool active) {
@@ -375,7 +375,7 @@ __device__ __forceinline__ void colour_pass_eig3(T* __restrict__ smem, const T* 
   const int ld1 = (int)n1d;
   // windows at the closure corner of the first patch
   const unsigned span = (unsigned)(2 * K * (n1d2 + n1d) + seg) * (unsigned)sizeof(T);  // below 4 GiB (launcher)
-  const Window<T> xw(x + (s2 * n1d2 + s1 * n1d + s0), span), bw(b + (s2 * n1d2 + s1 * n1d + s0), span);
+  const Win xw(x + (s2 * n1d2 + s1 * n1d + s0), span), bw(b + (s2 * n1d2 + s1 * n1d + s0), span);
   // byte offsets of the closure's planes and of its rows, as scalars: derived again inside divergent
   // branches they would become per-lane values and every access a loop over the lanes
   unsigned pl[n], rw[m];
@@ -391,8 +391,8 @@ __device__ __forceinline__ void colour_pass_eig3(T* __restrict__ smem, const T* 
   auto patch_constant = [&](int q) -> T {
     const unsigned lo = (unsigned)(2 * K * q) * (unsigned)sizeof(T);
     const unsigned hi = pl[2 * K] + (unsigned)(2 * K * (ld1 + q + 1)) * (unsigned)sizeof(T);
-    const T u = xw.load(0, (q == 0 && lo0) || lo1 || lo2 ? Window<T>::kOutside : lo);
-    const T v = xw.load(0, (q == P - 1 && hi0) || hi1 || hi2 ? Window<T>::kOutside : hi);
+    const T u = xw.load(0, Win::masked((q == 0 && lo0) || lo1 || lo2, lo));
+    const T v = xw.load(0, Win::masked((q == P - 1 && hi0) || hi1 || hi2, hi));
     return T(0.5) * (u + v);
   };
 
@@ -449,7 +449,7 @@ __device__ __forceinline__ void colour_pass_eig3(T* __restrict__ smem, const T* 
           const bool f0 = c == 0 || c == n - 1;  // x0 face, else x1 face
           // Dirichlet nodes count as 0 (the boundary entries of x are not read as values)
           const bool z = (col == 0 && lo0) || (col == seg - 1 && hi0) || (j1 == 0 && lo1) || (j1 == n - 1 && hi1);
-          const unsigned off = z ? Window<T>::kOutside : (unsigned)(__mul24(j1, ld1) + col) * (unsigned)sizeof(T);
+          const unsigned off = Win::masked(z, (unsigned)(__mul24(j1, ld1) + col) * (unsigned)sizeof(T));
           T w[n], r[m], Ee, Eo;
 #pragma unroll
           for (int j = 0; j < n; ++j) w[j] = xw.load(pl[j], off);
@@ -470,9 +470,9 @@ __device__ __forceinline__ void colour_pass_eig3(T* __restrict__ smem, const T* 
         const int t = (u - WB - WR) * 64 + lane;
         const int e = div_small<PPW * m>(t), g = t - e * (PPW * m), q = div_small<m>(g), i0 = g - q * m;
         if (t < NX && q < P) {
-          const unsigned off = (e == 0 ? lo2 : hi2)
-                                   ? Window<T>::kOutside
-                                   : (e == 0 ? 0u : pl[2 * K]) + (unsigned)(ld1 + 2 * K * q + 1 + i0) * (unsigned)sizeof(T);
+          const unsigned off =
+              Win::masked(e == 0 ? lo2 : hi2,
+                          (e == 0 ? 0u : pl[2 * K]) + (unsigned)(ld1 + 2 * K * q + 1 + i0) * (unsigned)sizeof(T));
           T w[m], r[m];
 #pragma unroll
           for (int i = 0; i < m; ++i) w[i] = xw.load(rw[i], off);
@@ -744,7 +744,7 @@ struct EigLds2 {
 //      (W F)                                                              -> PQ0, P1
 //   B  lines (q, a1)              x0: S^T b, minus the face terms, 1/(lam1 + lam0), S -> W2
 //   C  lines (q, i0)              x1: S, plus c, straight to global
-template <int K, typename T, bool POISON, typename SH>
+template <int K, typename T, bool POISON, typename SH, typename Win = Window<T>>
 __device__ __forceinline__ void colour_pass_eig2(T* __restrict__ smem, const T* __restrict__ b, T* __restrict__ x,
                                                  long long n1d, int p0, int p1, int cnt0, int cnt1, int groups0,
                                                  T sol_scale, unsigned blk, int tid, bool active) {
@@ -765,7 +765,7 @@ __device__ __forceinline__ void colour_pass_eig2(T* __restrict__ smem, const T* 
   const int ld1 = (int)n1d;
   // windows at the closure corner of the first patch
   const unsigned span = (unsigned)(2 * K * n1d + seg) * (unsigned)sizeof(T);  // below 4 GiB (launcher)
-  const Window<T> xw(x + (s1 * n1d + s0), span), bw(b + (s1 * n1d + s0), span);
+  const Win xw(x + (s1 * n1d + s0), span), bw(b + (s1 * n1d + s0), span);
   unsigned rw[m];  // byte offsets of the interior rows (scalars, as in the 3D form)
 #pragma unroll
   for (int i = 0; i < m; ++i) rw[i] = __builtin_amdgcn_readfirstlane((unsigned)((1 + i) * n1d) * (unsigned)sizeof(T));
@@ -811,8 +811,8 @@ __device__ __forceinline__ void colour_pass_eig2(T* __restrict__ smem, const T* 
           for (int j = 0; j < n; ++j) v[rr][j] = xw.load(0, off + (unsigned)j * st);
           // the mean of the patch's two extreme closure corners (a Dirichlet corner is 0)
           const unsigned hi = (unsigned)(2 * K * (ld1 + q + 1)) * (unsigned)sizeof(T);
-          cq[rr] = T(0.5) * (xw.load(0, (q == 0 && lo0) || lo1 ? Window<T>::kOutside : (unsigned)(2 * K * q) * (unsigned)sizeof(T)) +
-                             xw.load(0, (q == P - 1 && hi0) || hi1 ? Window<T>::kOutside : hi));
+          cq[rr] = T(0.5) * (xw.load(0, Win::masked((q == 0 && lo0) || lo1, (unsigned)(2 * K * q) * (unsigned)sizeof(T))) +
+                             xw.load(0, Win::masked((q == P - 1 && hi0) || hi1, hi)));
         }
       }
     }
@@ -940,7 +940,7 @@ __device__ __forceinline__ void colour_pass_eig2(T* __restrict__ smem, const T* 
 // patch, PPW consecutive patches along x0 per one-wave workgroup, and neither LDS nor a barrier.  The
 // residual b - h^(d-2) Abar x is summed row by row from the 1D patch rows (Sec. 3.1.1), then
 // x^I += residual / (h^(d-2) diagonal); without OLD (Boundary mode) the old x^I counts as 0.
-template <int D, typename T, bool OLD, int PPW>
+template <int D, typename T, bool OLD, int PPW, typename Win = Window<T>>
 __device__ __forceinline__ void colour_pass_q1(const T* __restrict__ b, T* __restrict__ x, long long n1d, int p0, int p1,
                                                int p2, int cnt0, int cnt1, int groups0, T res_scale, T sol_scale,
                                                unsigned blk, int tid, bool active) {
@@ -950,7 +950,7 @@ __device__ __forceinline__ void colour_pass_q1(const T* __restrict__ b, T* __res
   const int q = tid, seg = 2 * cb.count + 1;
   const long long n1d2 = n1d * n1d, origin = (D == 3 ? cb.s2 * n1d2 : 0) + cb.s1 * n1d + cb.s0;
   const unsigned span = (unsigned)((D == 3 ? 2 * n1d2 : 0) + 2 * n1d + seg) * (unsigned)sizeof(T);
-  const Window<T> xw(x + origin, span), bw(b + origin, span);
+  const Win xw(x + origin, span), bw(b + origin, span);
   const bool lo0 = cb.s0 == 0, hi0 = cb.s0 + seg - 1 == n1d - 1;
   const bool edge1[2] = {cb.s1 == 0, cb.s1 + 2 == n1d - 1};
   const bool edge2[2] = {D == 3 && cb.s2 == 0, D == 3 && cb.s2 + 2 == n1d - 1};
@@ -959,8 +959,8 @@ __device__ __forceinline__ void colour_pass_q1(const T* __restrict__ b, T* __res
   unsigned off[n];
 #pragma unroll
   for (int c = 0; c < n; ++c) off[c] = (unsigned)(2 * q + c) * (unsigned)sizeof(T);
-  if (q == 0 && lo0) off[0] = Window<T>::kOutside;
-  if (q == cb.count - 1 && hi0) off[2] = Window<T>::kOutside;
+  if (q == 0 && lo0) off[0] = Win::masked(true, off[0]);
+  if (q == cb.count - 1 && hi0) off[2] = Win::masked(true, off[2]);
   const unsigned centre = (unsigned)((D == 3 ? n1d2 : 0) + n1d) * (unsigned)sizeof(T);
   const T bv = bw.load(centre, off[1]);
   T v[J2][n][n];
@@ -2707,15 +2707,17 @@ __global__ __launch_bounds__((FusedTeams<D, K, T>::SH::NT * FusedTeams<D, K, T>:
 // The exact solve on the coarsest level: one patch, FP64 arithmetic for both precisions, one workgroup per
 // member; the boundary nodes of x become 0.  Lines as in the passes above: S^T along x2, x1 and x0, the
 // eigenvalue scaling, S along x0, x1 and x2 (2D: x1, x0, x0, x1).
-template <int D, int K, typename T>
-__global__ __launch_bounds__(256) void coarse_solve_kernel(FusedMembers mem) {
+template <int D, int K>
+struct CoarseLds {
+  static constexpr int m = 2 * K - 1, words = D == 3 ? m * m * m : m * m;  // doubles of one buffer
+};
+template <int D, int K, typename T, int NT>
+__device__ __forceinline__ void coarse_solve(double* __restrict__ w0, double* __restrict__ w1, const T* __restrict__ b,
+                                             T* __restrict__ x, int t) {
   constexpr int n = 2 * K + 1, m = 2 * K - 1, mm = m * m, L = D == 3 ? mm : m;
-  __shared__ double w0[L * m], w1[L * m];
-  const T* b = (const T*)mem.b[blockIdx.x];
-  T* x = (T*)mem.x[blockIdx.x];
-  const int t = threadIdx.x;
+  static_assert(NT >= L, "a line per thread");
   const DevTables<double>& tb = tab<double>(K);
-  for (int i = t; i < (D == 3 ? n * n * n : n * n); i += 256) {
+  for (int i = t; i < (D == 3 ? n * n * n : n * n); i += NT) {
     const int i0 = i % n, i1 = (i / n) % n, i2 = i / (n * n);
     if (i0 == 0 || i0 == n - 1 || i1 == 0 || i1 == n - 1 || (D == 3 && (i2 == 0 || i2 == n - 1))) x[i] = T(0);
   }
@@ -2773,6 +2775,289 @@ __global__ __launch_bounds__(256) void coarse_solve_kernel(FusedMembers mem) {
 #pragma unroll
     for (int i = 0; i < m; ++i) x[(1 + i) * st + base] = (T)(scale * u[i]);
   }
+}
+
+template <int D, int K, typename T>
+__global__ __launch_bounds__(256) void coarse_solve_kernel(FusedMembers mem) {
+  __shared__ double w[2 * CoarseLds<D, K>::words];
+  coarse_solve<D, K, T, 256>(w, w + CoarseLds<D, K>::words, (const T*)mem.b[blockIdx.x], (T*)mem.x[blockIdx.x],
+                             threadIdx.x);
+}
+
+// ------------------------------------------------------------------ the small levels of a V-cycle in one launch
+//
+// The V-cycle from x = 0 on a level of a few thousand nodes is a chain of short stages: as launches each costs
+// 2-4 us of which well under 1 us is work.  Here one workgroup per member holds right-hand side, iterate and
+// scratch of the levels 1..top in LDS and runs the whole chain, level by level, with barriers only.  A stage then
+// costs an LDS round trip, and the launches, the global round trips between the stages and the stores' drain at
+// each launch's end go.
+// Smoothing: the colour passes of a span of the whole grid, on LdsWindow.  Transfer: with x in the fine space and
+// R = P^T, the next right-hand side R b - R A x is summed axis by axis, each axis restricted as it is contracted
+// (RA, RM: P^T times the 1D matrices of a coarse cell's two fine cells), so the second and third axis work on half
+// and a quarter of the lines.  Measured, device time: 2D degree 3 FP64 level 3 and
+// below 38 us against 11 launches of 3.5-8 us and their gaps; 3D degree 2 FP32 level 2 36 us against 7 launches.  What
+// bounds it is one workgroup's chain of barriers, LDS round trips and dependent multiply-adds (16 passes of 1.7 us in
+// the first case); a copy of the reciprocal tables in LDS changed nothing.  Structure: P's columns of coarse nodes off the boundary vanish on fine boundary
+// nodes, so the fine residual's boundary entries never enter; values on coarse boundary nodes are left undefined
+// and never read.
+template <int D, int K, typename T, int TOP>
+struct CycleLds {
+  using SH = typename FusedTeams<D, K, T>::SH;
+  // four teams cover a colour of level 3 in 2D; with 512 threads a lane has 256 registers
+  static constexpr int TEAMS = D == 2 && K >= 4 ? 4 : FusedTeams<D, K, T>::N, NT = TEAMS * SH::NT;
+  static constexpr __host__ __device__ int n1d(int l) { return (K << l) + 1; }
+  static constexpr __host__ __device__ int stride(int l) {  // words of a level's vector
+    return even_up(n1d(l) * n1d(l) * (D == 3 ? n1d(l) : 1));
+  }
+  static constexpr __host__ __device__ int offset(int l) {  // level l: its iterate, then its right-hand side
+    int o = 0;
+    for (int i = 1; i < l; ++i) o += 2 * stride(i);
+    return o;
+  }
+  static constexpr int lds_team() {
+    if constexpr (K == 1) return 0;
+    else if constexpr (D == 3) return (EigLds3<K, SH>::total + 3) & ~3;
+    else return (EigLds2<K, SH>::total + 3) & ~3;
+  }
+  static constexpr int kTeam = lds_team();
+  static constexpr int nf = n1d(TOP), nc = n1d(TOP - 1);
+  static constexpr int kTransfer = D == 3 ? 3 * nc * nf * (nf + nc) : 3 * nc * nf;
+  static constexpr int kCoarse = 2 * CoarseLds<D, K>::words * (int)(8 / sizeof(T));
+  static constexpr int work = (offset(TOP + 1) + 3) & ~3;
+  static constexpr int total = work + max_of(max_of(kTeam * TEAMS, kTransfer), kCoarse);
+  static_assert(total * sizeof(T) <= 160 * 1024, "LDS of a compute unit");
+};
+
+// y: coarse nodes K C .. K C + K - 1 of one axis from the fine nodes 2K (C - 1) .. 2K (C + 1): rows of P^T times the
+// stiffness (STIFF) or the mass.
+template <int K, typename T, bool STIFF>
+__device__ __forceinline__ void restrict_matrix(const T (&f)[4 * K + 1], T (&y)[K]) {
+  using CT = gen::CellTables<T, K>;
+  constexpr int nf = 2 * K + 1;
+#pragma unroll
+  for (int a = 0; a < K; ++a) {
+    T s = T(0);
+    if (a == 0) {
+#pragma unroll
+      for (int j = 0; j < nf; ++j) s = fma(STIFF ? CT::RA[K * nf + j] : CT::RM[K * nf + j], f[j], s);
+    }
+#pragma unroll
+    for (int j = 0; j < nf; ++j) s = fma(STIFF ? CT::RA[a * nf + j] : CT::RM[a * nf + j], f[2 * K + j], s);
+    y[a] = s;
+  }
+}
+// the same nodes of P^T f
+template <int K, typename T>
+__device__ __forceinline__ void restrict_values(const T (&f)[4 * K + 1], T (&y)[K]) {
+  using CT = gen::CellTables<T, K>;
+  constexpr int np = K + 1;
+#pragma unroll
+  for (int a = 0; a < K; ++a) {
+    T s = a == 0 ? +f[2 * K] : T(0);
+#pragma unroll
+    for (int q = 1; q < 2 * K; ++q) {
+      if (a == 0) s = fma(CT::P[q * np + K], f[q], s);
+      if (CT::P[q * np + a] != T(0)) s = fma(CT::P[q * np + a], f[2 * K + q], s);
+    }
+    y[a] = s;
+  }
+}
+
+// bc = P^T (b - scale A x) on the interior of the coarse level; w: the scratch.
+template <int D, int K, typename T, int NT>
+__device__ __forceinline__ void cycle_restrict(T* __restrict__ w, const T* __restrict__ x, const T* __restrict__ b,
+                                               T* __restrict__ bc, int cells, T scale, int tid) {
+  constexpr int R = 4 * K + 1;
+  const int nf = 2 * K * cells + 1, nc = K * cells + 1, ci = K * cells;  // cells: coarse cells per axis
+  const int lines = D == 3 ? nf * nf : nf, plane = D == 3 ? nf * nf * nc : nf * nc;
+  // f <- entries 2K (C - 1) + q of a line (stride st); the cell left of the domain counts as 0
+  auto fetch = [&](const T* line, int st, int C, T (&f)[R]) {
+#pragma unroll
+    for (int q = 0; q < R; ++q) f[q] = q < 2 * K && C == 0 ? T(0) : line[(2 * K * (C - 1) + q) * st];
+  };
+  T f[R], y[K], z[K];
+  // x0: M x, A x, R b
+  for (int t = tid; t < lines * cells; t += NT) {
+    const int C = (int)((unsigned)t / (unsigned)lines), l = t - C * lines, o = l * nc + K * C;
+    fetch(x + l * nf, 1, C, f);
+    restrict_matrix<K, T, false>(f, y);
+#pragma unroll
+    for (int a = 0; a < K; ++a) w[o + a] = y[a];
+    restrict_matrix<K, T, true>(f, y);
+#pragma unroll
+    for (int a = 0; a < K; ++a) w[plane + o + a] = y[a];
+    fetch(b + l * nf, 1, C, f);
+    restrict_values<K, T>(f, y);
+#pragma unroll
+    for (int a = 0; a < K; ++a) w[2 * plane + o + a] = y[a];
+  }
+  __syncthreads();
+  if constexpr (D == 3) {
+    // x1: M M, A M + M A, R R b
+    T* w2 = w + 3 * plane;
+    const int plane2 = nf * nc * nc;
+    for (int t = tid; t < nf * cells * ci; t += NT) {
+      const int g = (int)((unsigned)t / (unsigned)ci), c0 = t - g * ci;
+      const int C = (int)((unsigned)g / (unsigned)nf), j2 = g - C * nf;
+      const int i = j2 * nf * nc + c0, o = (j2 * nc + K * C) * nc + c0;
+      fetch(w + i, nc, C, f);
+      restrict_matrix<K, T, false>(f, y);
+#pragma unroll
+      for (int a = 0; a < K; ++a) w2[o + a * nc] = y[a];
+      restrict_matrix<K, T, true>(f, y);
+      fetch(w + plane + i, nc, C, f);
+      restrict_matrix<K, T, false>(f, z);
+#pragma unroll
+      for (int a = 0; a < K; ++a) w2[plane2 + o + a * nc] = y[a] + z[a];
+      fetch(w + 2 * plane + i, nc, C, f);
+      restrict_values<K, T>(f, y);
+#pragma unroll
+      for (int a = 0; a < K; ++a) w2[2 * plane2 + o + a * nc] = y[a];
+    }
+    __syncthreads();
+  }
+  // the last axis: A (M M) + M (A M + M A), 2D A M + M A
+  const T* in = D == 3 ? w + 3 * plane : w;
+  const int step = D == 3 ? nf * nc * nc : plane, st = D == 3 ? nc * nc : nc, cols = D == 3 ? ci * ci : ci;
+  for (int t = tid; t < cols * cells; t += NT) {
+    const int C = (int)((unsigned)t / (unsigned)cols), r = t - C * cols;
+    const int c1 = D == 3 ? (int)((unsigned)r / (unsigned)ci) : 0, i = D == 3 ? r + c1 : r;  // c1 * nc + c0
+    fetch(in + i, st, C, f);
+    restrict_matrix<K, T, true>(f, y);
+    fetch(in + step + i, st, C, f);
+    restrict_matrix<K, T, false>(f, z);
+#pragma unroll
+    for (int a = 0; a < K; ++a) z[a] += y[a];
+    fetch(in + 2 * step + i, st, C, f);
+    restrict_values<K, T>(f, y);
+#pragma unroll
+    for (int a = 0; a < K; ++a) bc[(K * C + a) * st + i] = fma(-scale, z[a], y[a]);
+  }
+  __syncthreads();
+}
+
+// x += P xc; w: the scratch.
+template <int D, int K, typename T, int NT>
+__device__ __forceinline__ void cycle_prolongate(T* __restrict__ w, const T* __restrict__ xc, T* __restrict__ x, int cells,
+                                                 int tid) {
+  using CT = gen::CellTables<T, K>;
+  constexpr int np = K + 1;
+  const int nf = 2 * K * cells + 1, nc = K * cells + 1, fi = nf - 1;
+  const int lines = D == 3 ? nc * nc : nc;
+  // fine nodes q = 0 .. 2K - 1 of a coarse cell's line from its coarse nodes
+  auto expand = [&](const T (&f)[np], int q) -> T {
+    T s = T(0);
+#pragma unroll
+    for (int a = 0; a < np; ++a)
+      if (CT::P[q * np + a] != T(0)) s = fma(CT::P[q * np + a], f[a], s);
+    return s;
+  };
+  T f[np];
+  for (int t = tid; t < lines * cells; t += NT) {
+    const int C = (int)((unsigned)t / (unsigned)lines), l = t - C * lines;
+#pragma unroll
+    for (int a = 0; a < np; ++a) f[a] = xc[l * nc + K * C + a];
+#pragma unroll
+    for (int q = 0; q < 2 * K; ++q) w[l * nf + 2 * K * C + q] = expand(f, q);
+  }
+  __syncthreads();
+  const T* in = w;
+  if constexpr (D == 3) {
+    T* w2 = w + nc * nc * nf;
+    for (int t = tid; t < nc * cells * fi; t += NT) {
+      const int g = (int)((unsigned)t / (unsigned)fi), j0 = t - g * fi;
+      const int C = (int)((unsigned)g / (unsigned)nc), c2 = g - C * nc;
+#pragma unroll
+      for (int a = 0; a < np; ++a) f[a] = w[(c2 * nc + K * C + a) * nf + j0];
+#pragma unroll
+      for (int q = 0; q < 2 * K; ++q) w2[(c2 * nf + 2 * K * C + q) * nf + j0] = expand(f, q);
+    }
+    __syncthreads();
+    in = w2;
+  }
+  const int st = D == 3 ? nf * nf : nf, cols = D == 3 ? fi * fi : fi;
+  for (int t = tid; t < cols * cells; t += NT) {
+    const int C = (int)((unsigned)t / (unsigned)cols), r = t - C * cols;
+    const int j1 = D == 3 ? (int)((unsigned)r / (unsigned)fi) : 0, i = D == 3 ? r + j1 : r;  // j1 * nf + j0
+#pragma unroll
+    for (int a = 0; a < np; ++a) f[a] = in[(K * C + a) * st + i];
+#pragma unroll
+    for (int q = 0; q < 2 * K; ++q) x[(2 * K * C + q) * st + i] += expand(f, q);
+  }
+  __syncthreads();
+}
+
+struct CycleMembers {
+  const void* b[kMaxGroup];
+  void* x[kMaxGroup];
+  int top[kMaxGroup];
+};
+
+template <int D, int K, typename T, int TOP>
+__global__ __launch_bounds__((CycleLds<D, K, T, TOP>::NT)) void cycle_kernel(CycleMembers mem, int post_reverse) {
+  using C = CycleLds<D, K, T, TOP>;
+  using SH = typename C::SH;
+  constexpr int TEAMS = C::TEAMS, NT = C::NT, PPW = SH::PPW;
+  __shared__ __align__(16) T smem[C::total];
+  const int team = __builtin_amdgcn_readfirstlane((int)threadIdx.x / SH::NT), tid = threadIdx.x;
+  const int top = mem.top[blockIdx.x];
+  T* work = smem + C::work;
+  {
+    const T* b = (const T*)mem.b[blockIdx.x];
+    const int o = C::offset(top), s = C::stride(top), N = C::n1d(top) * C::n1d(top) * (D == 3 ? C::n1d(top) : 1);
+    for (int i = tid; i < N; i += NT) smem[o + s + i] = b[i];
+  }
+  // top .. 2, the coarse solve, 2 .. top
+  for (int step = 0; step < 2 * top - 1; ++step) {
+    const bool down = step < top;
+    const int l = down ? top - step : step - top + 2;
+    const int n = C::n1d(l), s = C::stride(l), half = 1 << (l - 1);
+    T* x = smem + C::offset(l);
+    const T* b = x + s;
+    if (l == 1) {
+      __syncthreads();
+      double* w = reinterpret_cast<double*>(work);
+      coarse_solve<D, K, T, NT>(w, w + CoarseLds<D, K>::words, b, x, tid);
+      __syncthreads();
+      continue;
+    }
+    if (down) {
+      for (int i = tid; i < s; i += NT) x[i] = T(0);
+      __syncthreads();
+    } else {
+      cycle_prolongate<D, K, T, NT>(work, smem + C::offset(l - 1), x, half, tid);
+    }
+    const T res_scale = D == 3 ? T(1) / T(1 << l) : T(1), sol_scale = D == 3 ? T(1 << l) : T(1);
+    const bool reverse = !down && post_reverse;
+    for (int ci = 0; ci < (1 << D); ++ci) {
+      const int c = reverse ? (1 << D) - 1 - ci : ci;
+      const int p0 = c & 1, p1 = (c >> 1) & 1, p2 = (c >> 2) & 1;
+      const int cnt0 = half - p0, cnt1 = half - p1, cnt2 = D == 3 ? half - p2 : 1;
+      const int groups0 = (cnt0 + PPW - 1) / PPW, blocks = groups0 * cnt1 * cnt2;
+      for (int base = 0; base < blocks; base += TEAMS) {
+        const int k = base + team;
+        const bool active = k < blocks;
+        const unsigned blk = (unsigned)(active ? k : 0);
+        T* tm = work + team * C::kTeam;
+        const int tt = tid - team * SH::NT;
+        if constexpr (K == 1)
+          colour_pass_q1<D, T, true, PPW, LdsWindow<T>>(b, x, n, p0, p1, p2, cnt0, cnt1, groups0, res_scale, sol_scale,
+                                                        blk, tt, active);
+        else if constexpr (D == 3)
+          colour_pass_eig3<K, T, false, SH, LdsWindow<T>>(tm, b, x, n, p0, p1, p2, cnt0, cnt1, groups0, sol_scale, blk,
+                                                          tt, active);
+        else
+          colour_pass_eig2<K, T, false, SH, LdsWindow<T>>(tm, b, x, n, p0, p1, cnt0, cnt1, groups0, sol_scale, blk, tt,
+                                                          active);
+        __syncthreads();
+      }
+    }
+    if (down)
+      cycle_restrict<D, K, T, NT>(work, x, b, smem + C::offset(l - 1) + C::stride(l - 1), half, res_scale, tid);
+  }
+  T* xo = (T*)mem.x[blockIdx.x];
+  const int o = C::offset(top), N = C::n1d(top) * C::n1d(top) * (D == 3 ? C::n1d(top) : 1);
+  for (int i = tid; i < N; i += NT) xo[i] = smem[o + i];
 }
 
 // ------------------------------------------------------------------ host side
@@ -3134,13 +3419,71 @@ static hipError_t with_degree(int dim, int k, F f) {
   return hipErrorInvalidValue;
 }
 
+// The highest level of cycle_kernel per (dim, degree, precision): 1 where one workgroup loses to the launches it
+// saves or its LDS does not suffice.  Four CG iterations with the cycle on the level as preconditioner, us, with the
+// cycle up to the level below against up to it: 2D degree 1 level 5 401 / 318, level 6 428 / 401; degree 2 level 4
+// FP32 381 / 347, level 5 476 / 541 (not taken); degree 3 level 4 FP32 485 / 455, FP64 518 / 528 (not taken); degree
+// 4 level 3 388 / 325, level 4 475 / 560 (not taken); degree 7 level 3 FP32 520 / 450, FP64 687 / 688.  3D degree 1
+// level 3 FP32 487 / 455, FP64 485 / 501 (not taken); degree 2 level 2 429 / 341, level 3 621 / 749 (not taken);
+// degree 3 level 2 494 / 390, FP64 545 / 440; degree 4 level 2 FP32 563 / 458.
+template <int D, int K, typename T>
+struct CycleTop {
+  static constexpr bool f32 = sizeof(T) == 4;
+  static constexpr int value = D == 2 ? (K == 1 ? 6 : K == 2 ? 4 : K == 3 && f32 ? 4 : 3)
+                                      : (K == 1 ? (f32 ? 3 : 2) : K <= 3 || (K == 4 && f32) ? 2 : 1);
+};
+
+int cycle_top(int dim, int k, int prec) {
+  int top = 1;
+  (void)with_degree(dim, k, [&](auto d, auto kk) {
+    constexpr int D = decltype(d)::value, K = decltype(kk)::value;
+    top = prec == 0 ? CycleTop<D, K, double>::value : CycleTop<D, K, float>::value;
+    return hipSuccess;
+  });
+  return top;
+}
+
+template <int D, int K, typename T>
+static hipError_t cycle_launch(const ColourPassMember* mem, int nm, bool post_reverse, hipStream_t st) {
+  constexpr int TOP = CycleTop<D, K, T>::value;
+  if constexpr (TOP < 2) {
+    return hipErrorInvalidValue;
+  } else {
+    for (int i0 = 0; i0 < nm; i0 += kMaxGroup) {
+      const int n = nm - i0 < kMaxGroup ? nm - i0 : kMaxGroup;
+      CycleMembers cm{};
+      for (int i = 0; i < n; ++i) {
+        if (mem[i0 + i].g.level < 1 || mem[i0 + i].g.level > TOP) return hipErrorInvalidValue;
+        cm.b[i] = mem[i0 + i].b;
+        cm.x[i] = mem[i0 + i].x;
+        cm.top[i] = mem[i0 + i].g.level;
+      }
+      hipLaunchKernelGGL((cycle_kernel<D, K, T, TOP>), dim3(n), dim3(CycleLds<D, K, T, TOP>::NT), 0, st, cm,
+                         post_reverse ? 1 : 0);
+      hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  }
+}
+
+hipError_t launch_cycle(int dim, int k, int prec, bool post_reverse, const ColourPassMember* mem, int nm,
+                        hipStream_t st) {
+  return with_degree(dim, k, [&](auto d, auto kk) {
+    constexpr int D = decltype(d)::value, K = decltype(kk)::value;
+    return prec == 0 ? cycle_launch<D, K, double>(mem, nm, post_reverse, st)
+                     : cycle_launch<D, K, float>(mem, nm, post_reverse, st);
+  });
+}
+
 // Spans from level 2 up, [dim - 2][k - 1][prec], where a fused step takes less device time than its single passes,
 // or up to 10% more (it also saves the host 2.4 us per launch).  One step, us, single passes against fused, FP32 /
 // FP64: 3D degree 1 levels 2-4 17-20 / 18-22 against 10-15; degree 2 22, 25, 25 against 19, 24, 26; degree 3 30, 31,
 // 31 against 23, 29, 34; degree 4 level 2 32 / 38 against 28 / 39, level 4 36 / 44 against 43 / 58 (not taken: a
 // workgroup runs on one compute unit, and four teams saturate its vector units); degree 7 level 2 47 / 66 against
 // 62 / 129.  2D degree 1 levels 2-6 6.6-9.5 against 3.4-5.8; degree 4 level 3 12 / 15 against 9.5 / 14, level 5
-// 13.9 / 15.6 against 11.9 / 16.8; degree 7 level 3 16 / 22 against 14 / 21, level 5 FP64 23 against 28.
+// 13.9 / 15.6 against 11.9 / 16.8; degree 7 level 3 16 / 22 against 14 / 21, level 5 FP64 23 against 28.  Levels up
+// to cycle_top() serve the additive step only (corrections there run in the cycle's launch).
 static const char* const kFusedSpans[2][7][2] = {
     {{"222111", "222111"},  // 2D; {FP64, FP32}
      {"222111", "222111"},
