@@ -1430,7 +1430,7 @@ hipError_t launch_operator(const LevelGeom& g, int prec, const void* x, const vo
 namespace {
 // out[0] = sum of part[0..n) in a fixed order (one workgroup of blockDim.x <= 1024 threads)
 __global__ __launch_bounds__(1024) void sum_parts_kernel(const double* __restrict__ part, int n,
-                                                          double* __restrict__ out) {
+                                                          double* __restrict__ out, double* __restrict__ host) {
   __shared__ double red[1024];
   const int nt = blockDim.x, tid = threadIdx.x;
   double s = 0.0;
@@ -1442,11 +1442,14 @@ __global__ __launch_bounds__(1024) void sum_parts_kernel(const double* __restric
     if (tid < w) red[tid] += red[tid + w];
     __syncthreads();
   }
-  if (tid == 0) out[0] = red[0];
+  if (tid == 0) {
+    out[0] = red[0];
+    if (host) *host = red[0];
+  }
 }
 
-hipError_t sum_parts(const double* part, long long n, double* out, hipStream_t st) {
-  hipLaunchKernelGGL(sum_parts_kernel, dim3(1), dim3(n > 4096 ? 1024 : 256), 0, st, part, (int)n, out);
+hipError_t sum_parts(const double* part, long long n, double* out, double* host, hipStream_t st) {
+  hipLaunchKernelGGL(sum_parts_kernel, dim3(1), dim3(n > 4096 ? 1024 : 256), 0, st, part, (int)n, out, host);
   return hipGetLastError();
 }
 
@@ -1486,7 +1489,7 @@ hipError_t fused_op_k(const LevelGeom& g, const double* x, const double* b, doub
 }
 
 hipError_t fused_op(const LevelGeom& g, const double* x, const double* b, double* y, double* part, long long max_parts,
-                    double* out, hipStream_t st, bool* fused) {
+                    double* out, hipStream_t st, bool* fused, double* host) {
   *fused = false;
   const long long n = fused_parts(g);
   // no fused form, or more partial sums than the buffer holds: the caller takes the unfused path
@@ -1502,7 +1505,7 @@ hipError_t fused_op(const LevelGeom& g, const double* x, const double* b, double
     case 7: e = fused_op_k<7>(g, x, b, y, part, st); break;
   }
   if (e != hipSuccess) return e;
-  e = sum_parts(part, n, out, st);
+  if (out) e = sum_parts(part, n, out, host, st);
   if (e == hipSuccess) *fused = true;
   return e;
 }
@@ -1511,13 +1514,13 @@ hipError_t fused_op(const LevelGeom& g, const double* x, const double* b, double
 long long fused_reduction_parts(const LevelGeom& g) { return fused_parts(g); }
 
 hipError_t launch_residual_norm2(const LevelGeom& g, const double* x, const double* b, double* part,
-                                 long long max_parts, double* out, hipStream_t st, bool* fused) {
-  return fused_op(g, x, b, nullptr, part, max_parts, out, st, fused);
+                                 long long max_parts, double* out, hipStream_t st, bool* fused, double* host) {
+  return fused_op(g, x, b, nullptr, part, max_parts, out, st, fused, host);
 }
 
 hipError_t launch_operator_pq(const LevelGeom& g, const double* p, double* q, double* part, long long max_parts,
                               double* out, hipStream_t st, bool* fused) {
-  return fused_op(g, p, nullptr, q, part, max_parts, out, st, fused);
+  return fused_op(g, p, nullptr, q, part, max_parts, out, st, fused, nullptr);
 }
 
 hipError_t launch_prolongate_add(const LevelGeom& fine, int prec, const void* e, void* xf, hipStream_t st) {

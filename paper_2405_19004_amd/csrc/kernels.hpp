@@ -16,9 +16,7 @@ enum : int {
   kScPQ = 10,    // p.A p                         (written together with slot 11)
   kScRR = 2,     // r.r after the update          (written together with kScRZOld)
   kScRZOld = 3,  // r_new . z_old (flexible beta)
-  kScRZNew = 4,  // r_new . z_new                 (written together with kScAux)
-  kScAux = 5,
-  kScBeta = 6,
+  kScRZNew = 4,  // r_new . z_new
   kScBB = 7,     // b.b
   kScTrue = 8,   // true residual norm squared    (written together with kScAux2)
   kScAux2 = 9,
@@ -112,14 +110,14 @@ hipError_t launch_operator(const LevelGeom& g, int prec, const void* x, const vo
 // Per-workgroup partial sums the two fused operator forms below take on level g (0: no fused
 // form on that level).
 long long fused_reduction_parts(const LevelGeom& g);
-// q = A p in FP64 with out[0] = p.q summed in a fixed order from per-workgroup partials (at most
-// max_parts of them); *fused = false (nothing launched) where that form is not available.
+// q = A p in FP64 with the partials of p.q per workgroup (at most max_parts) in part and, when out is not null, out[0] =
+// their sum in a fixed order; *fused = false (nothing launched) where that form is not available.
 hipError_t launch_operator_pq(const LevelGeom& g, const double* p, double* q, double* part, long long max_parts,
                               double* out, hipStream_t st, bool* fused);
 // out[0] = |b - A x|^2 (interior, FP64) summed in a fixed order from per-workgroup partials, the
 // residual itself not stored; *fused = false (nothing launched) where that form is not available.
 hipError_t launch_residual_norm2(const LevelGeom& g, const double* x, const double* b, double* part,
-                                 long long max_parts, double* out, hipStream_t st, bool* fused);
+                                 long long max_parts, double* out, hipStream_t st, bool* fused, double* host);
 // Restriction P^T of a fine-level vector (fine boundary entries ignored, coarse boundary written 0);
 // t is scratch of restrict_scratch_elems(fine) elements (none in 2D: one kernel, no intermediate).
 hipError_t launch_restrict(const LevelGeom& fine, int prec, const void* rf, void* rc, void* t, hipStream_t st);
@@ -152,23 +150,26 @@ int reduction_parts();  // partial slots the reductions use (pairs: 2x this many
 hipError_t launch_fill(int prec, void* x, long long n, double v, hipStream_t st);
 hipError_t launch_cast(int from_prec, const void* src, void* dst, long long n, hipStream_t st);
 // dst = interior of src, out = |dst|^2, *bad |= non-finite entries; optionally dst32 = (float)dst
-// and zero = 0 over the same range
+// and zero = 0 over the same range; host, host_bad: pinned copies of out[0] and *bad
 hipError_t launch_copy_interior_norm(int dim, long long n1d, const double* src, double* dst, double* partial,
                                      double* out, int* bad, hipStream_t st, float* dst32 = nullptr,
-                                     double* zero = nullptr);
+                                     double* zero = nullptr, double* host = nullptr, int* host_bad = nullptr);
 hipError_t launch_dot2(const double* a, const double* b, const double* c, const double* d, long long n,
-                       double* partial, double* out, hipStream_t st);
-// x += alpha p, r -= alpha q with alpha = rz / pq, partials of r.r and r.z, and r32 = (float) r
-// when r32 != null.  z is the previous preconditioned residual: the FP32 z32 (widened exactly)
-// when non-null, else the FP64 z.
+                       double* partial, double* out, hipStream_t st, double* host = nullptr);
+// The partials of a.b (b FP64, or the FP32 b32 widened exactly, when non-null) only: dot_parts(n) pairs, sum in slot 0.
+hipError_t launch_dot_parts(const double* a, const double* b, const float* b32, long long n, double* partial,
+                            hipStream_t st);
+int dot_parts(long long n);
+// x += alpha p, r -= alpha q with alpha = rz / pq (rz: sc[RZNew]; pq: the sum of n_pq entries of pq_part at the
+// stride, or sc[PQ] when n_pq is 0), r.r, r.z and pq to sc and rz to sc[RZ], all of what the stopping test reads also to
+// host, and r32 = (float) r when r32 != null.  z is the previous preconditioned residual: the FP32 z32 (widened
+// exactly) when non-null, else the FP64 z.  pq_part and partial do not overlap.
 hipError_t launch_cg_update(double* x, double* r, const double* p, const double* q, const double* z, const float* z32,
-                            long long n, double* sc, double* partial, float* r32, hipStream_t st);
-// out[0] = r.z32 with z32 widened exactly (deterministic)
-hipError_t launch_dot_rz32(const float* z32, const double* r, long long n, double* partial, double* out,
-                           hipStream_t st);
-hipError_t launch_cg_beta(double* sc, int flexible, hipStream_t st);
-// p = z + beta p (z32 widened exactly when non-null, else z)
-hipError_t launch_cg_direction(double* p, const double* z, const float* z32, long long n, const double* sc,
-                               hipStream_t st);
+                            long long n, const double* pq_part, int n_pq, int pq_stride, double* sc, double* partial,
+                            float* r32, double* host, hipStream_t st);
+// p = z + beta p (z32 widened exactly when non-null, else z), beta = (rz_new - flexible r.z_old) / rz with rz_new, which
+// becomes sc[RZNew], the sum of the partials of r.z; first: p = z.
+hipError_t launch_cg_direction(double* p, const double* z, const float* z32, long long n, const double* rz_part,
+                               bool flexible, bool first, double* sc, hipStream_t st);
 
 }  // namespace vps

@@ -455,7 +455,7 @@ const float* cg_z32(const Problem* p, int mode) {
   return mode == 1 ? static_cast<const float*>(p->lv[p->L].x[1]) : nullptr;
 }
 
-// z = M r with the problem's CG vectors, and sc[RZNew] = r.z.  Mixed mode: the FP32 copy of r
+// z = M r with the problem's CG vectors, and the partials of r.z in partial.  Mixed mode: the FP32 copy of r
 // must already be in the level-L FP32 rhs (cg_update or pcg_begin writes it), and z stays the FP32
 // result in the level-L FP32 iterate (cg_z32): its consumers widen it exactly as they read it.
 Status precondition_launch(Problem* p, int mode) {
@@ -464,12 +464,12 @@ Status precondition_launch(Problem* p, int mode) {
   // one-level hierarchy) writes every node of z, so z is not cleared first
   if (mode == 0) {
     VPS_TRY(vcycle_top(p, 0, p->L, p->r, p->z, true));
-    VPS_HIP(launch_dot2(p->r, p->z, nullptr, nullptr, N, p->partial, p->sc + kScRZNew, p->stream));
+    VPS_HIP(launch_dot_parts(p->r, p->z, nullptr, N, p->partial, p->stream));
     return Status::ok();
   }
   LevelBuffers& B = p->lv[p->L];
   VPS_TRY(vcycle_top(p, 1, p->L, B.b[1], B.x[1], true));
-  VPS_HIP(launch_dot_rz32((const float*)B.x[1], p->r, N, p->partial, p->sc + kScRZNew, p->stream));
+  VPS_HIP(launch_dot_parts(p->r, nullptr, (const float*)B.x[1], N, p->partial, p->stream));
   return Status::ok();
 }
 
@@ -542,11 +542,8 @@ Status precondition_group(Problem* const* ps, int n, int mode) {
   for (int i = 0; i < n; ++i) {
     Problem* p = ps[i];
     const long long N = p->lv[p->L].N;
-    if (mode == 0)
-      VPS_HIP(launch_dot2(p->r, p->z, nullptr, nullptr, N, p->partial, p->sc + kScRZNew, p->stream));
-    else
-      VPS_HIP(launch_dot_rz32((const float*)p->lv[p->L].x[1], p->r, N, p->partial, p->sc + kScRZNew,
-                               p->stream));
+    VPS_HIP(launch_dot_parts(p->r, p->z, mode == 0 ? nullptr : (const float*)p->lv[p->L].x[1], N, p->partial,
+                             p->stream));
   }
   return Status::ok();
 }
@@ -559,9 +556,8 @@ Status pcg_begin_launch(Problem* p, int mode, const double* b, double* x, CgStat
   VPS_HIP(hipMemsetAsync(p->bad, 0, sizeof(int), p->stream));
   // r = b (interior), x = 0 and, mixed, the FP32 copy of r (the FP32 V-cycle's input) in one pass
   VPS_HIP(launch_copy_interior_norm(p->dim, p->lv[p->L].g.n1d, b, p->r, p->partial, p->sc + kScBB, p->bad, p->stream,
-                                    mode == 1 ? static_cast<float*>(p->lv[p->L].b[1]) : nullptr, x));
-  VPS_HIP(hipMemcpyAsync(p->host_sc, p->sc, kScCount * sizeof(double), hipMemcpyDeviceToHost, p->stream));
-  VPS_HIP(hipMemcpyAsync(p->host_bad, p->bad, sizeof(int), hipMemcpyDeviceToHost, p->stream));
+                                    mode == 1 ? static_cast<float*>(p->lv[p->L].b[1]) : nullptr, x,
+                                    p->host_sc + kScBB, p->host_bad));
   return Status::ok();
 }
 
@@ -579,11 +575,7 @@ Status pcg_begin_check(Problem* p, CgState* cs) {
 
 Status pcg_begin_after_precond(Problem* p, int mode) {
   const long long N = p->lv[p->L].N;
-  VPS_HIP(launch_cg_beta(p->sc, 0, p->stream));  // rz <- rz_new (beta unused here)
-  if (mode == 1)
-    VPS_HIP(launch_cast(1, cg_z32(p, mode), p->p, N, p->stream));  // p = z, widened exactly
-  else
-    VPS_HIP(hipMemcpyAsync(p->p, p->z, N * sizeof(double), hipMemcpyDeviceToDevice, p->stream));
+  VPS_HIP(launch_cg_direction(p->p, p->z, cg_z32(p, mode), N, p->partial, false, true, p->sc, p->stream));
   return Status::ok();
 }
 
@@ -600,15 +592,31 @@ Status pcg_iterate_launch(Problem* p, int mode, double* x, CgState* cs) {
   (void)mode;
   const long long N = p->lv[p->L].N;
   bool fused = false;
-  VPS_HIP(launch_operator_pq(p->geom(p->L), p->p, p->q, p->partial, p->n_partial, p->sc + kScPQ, p->stream,
-                             &fused));
+  // The partials of p.q stay for the CG step to add where they fit behind its own (r.r, r.z) and are at most 4096, 32 KB
+  // that its every workgroup reads; else they are summed first.
+  const int parts = dot_parts(N);
+  double* pq_part = p->partial + 2 * parts;
+  const long long room = p->n_partial - 2 * parts, n_fused = fused_reduction_parts(p->geom(p->L));
+  int n_pq = 0, pq_stride = 1;
+  if (n_fused > 0 && n_fused <= std::min<long long>(room, 4096)) {
+    VPS_HIP(launch_operator_pq(p->geom(p->L), p->p, p->q, pq_part, room, nullptr, p->stream, &fused));
+    if (fused) n_pq = (int)n_fused;
+  } else {
+    VPS_HIP(launch_operator_pq(p->geom(p->L), p->p, p->q, p->partial, p->n_partial, p->sc + kScPQ, p->stream, &fused));
+  }
   if (!fused) {
     VPS_HIP(launch_operator(p->geom(p->L), 0, p->p, nullptr, p->q, p->stream));
-    VPS_HIP(launch_dot2(p->p, p->q, nullptr, nullptr, N, p->partial, p->sc + kScPQ, p->stream));
+    if (2 * parts <= room) {
+      VPS_HIP(launch_dot_parts(p->p, p->q, nullptr, N, pq_part, p->stream));
+      n_pq = parts;
+      pq_stride = 2;
+    } else {
+      VPS_HIP(launch_dot2(p->p, p->q, nullptr, nullptr, N, p->partial, p->sc + kScPQ, p->stream));
+    }
   }
   float* r32 = mode == 1 ? static_cast<float*>(p->lv[p->L].b[1]) : nullptr;  // input of the FP32 V-cycle
-  VPS_HIP(launch_cg_update(x, p->r, p->p, p->q, p->z, cg_z32(p, mode), N, p->sc, p->partial, r32, p->stream));
-  VPS_HIP(hipMemcpyAsync(p->host_sc, p->sc, kScCount * sizeof(double), hipMemcpyDeviceToHost, p->stream));
+  VPS_HIP(launch_cg_update(x, p->r, p->p, p->q, p->z, cg_z32(p, mode), N, pq_part, n_pq, pq_stride, p->sc,
+                           p->partial, r32, p->host_sc, p->stream));
   (void)cs;
   return Status::ok();
 }
@@ -639,8 +647,8 @@ Status pcg_after_precond(Problem* p, int mode) {
   const long long N = p->lv[p->L].N;
   // flexible (Polak-Ribiere) beta whenever the preconditioner is not symmetric: FP32 V-cycle
   // (rounding) or the literal colour order after the coarse correction
-  VPS_HIP(launch_cg_beta(p->sc, (mode == 1 || p->post_same_order) ? 1 : 0, p->stream));
-  VPS_HIP(launch_cg_direction(p->p, p->z, cg_z32(p, mode), N, p->sc, p->stream));
+  VPS_HIP(launch_cg_direction(p->p, p->z, cg_z32(p, mode), N, p->partial, mode == 1 || p->post_same_order, false,
+                              p->sc, p->stream));
   return Status::ok();
 }
 
@@ -658,12 +666,12 @@ Status pcg_end_launch(Problem* p, const double* b, const double* x, const CgStat
   // |b - A x|^2 in one pass where a fused operator form serves the level, else through q
   bool fused = false;
   VPS_HIP(launch_residual_norm2(p->geom(p->L), x, b, p->partial, p->n_partial, p->sc + kScTrue, p->stream,
-                                &fused));
+                                &fused, p->host_sc + kScTrue));
   if (!fused) {
     VPS_HIP(launch_operator(p->geom(p->L), 0, x, b, p->q, p->stream));  // q = b - A x (interior)
-    VPS_HIP(launch_dot2(p->q, p->q, nullptr, nullptr, N, p->partial, p->sc + kScTrue, p->stream));
+    VPS_HIP(launch_dot2(p->q, p->q, nullptr, nullptr, N, p->partial, p->sc + kScTrue, p->stream,
+                        p->host_sc + kScTrue));
   }
-  VPS_HIP(hipMemcpyAsync(p->host_sc, p->sc, kScCount * sizeof(double), hipMemcpyDeviceToHost, p->stream));
   *pending = true;
   return Status::ok();
 }
