@@ -97,7 +97,7 @@ def colour_pass_lds_bytes_3d(k, es, ppw):
 def smoother_source_hash():
     import hashlib
     h = hashlib.sha256()
-    for f in ("smoother.hip", "device_common.hpp"):
+    for f in ("smoother.hip", "colour_pass.hpp", "device_common.hpp"):
         h.update(open(os.path.join(ROOT, "paper_2405_19004_amd", "csrc", f), "rb").read())
     return h.hexdigest()[:16]
 

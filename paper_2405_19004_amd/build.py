@@ -25,7 +25,9 @@ COMMON = [
     "-I" + os.path.join(ROOT, "include"), "-I" + CSRC, "-I" + os.path.join(HERE, "_build", "gen"),
     "-Wno-unused-command-line-argument",
 ]
-SOURCES = ["smoother.hip", "grid.hip", "vector.hip", "tables.cpp", "problem.cpp", "capi.cpp", "server.cpp"]
+# the reason stands at the top of the file
+EXTRA = {"small_levels.hip": ["-mllvm", "-disable-machine-licm"]}
+SOURCES = ["smoother.hip", "small_levels.hip", "grid.hip", "vector.hip", "tables.cpp", "problem.cpp", "capi.cpp", "server.cpp"]
 
 
 def _hipcc():
@@ -37,7 +39,7 @@ def _hipcc():
 
 def _compile(src, verbose):
     out = os.path.join(BUILD, os.path.splitext(src)[0] + ".o")
-    cmd = [_hipcc()] + COMMON + ["-c", os.path.join(CSRC, src), "-o", out]
+    cmd = [_hipcc()] + COMMON + EXTRA.get(src, []) + ["-c", os.path.join(CSRC, src), "-o", out]
     if verbose:
         print(" ".join(cmd), flush=True)
     r = subprocess.run(cmd, capture_output=True, text=True)

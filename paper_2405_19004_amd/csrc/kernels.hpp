@@ -23,7 +23,8 @@ enum : int {
   kScCount = 16
 };
 
-hipError_t init_smoother_tables();
+hipError_t init_smoother_tables();     // smoother.hip, and through it
+hipError_t init_small_level_tables();  // small_levels.hip
 
 // Colour-pass kernels: multiplicative (residual, then x^I += A_j^{-1} r), additive
 // (x^I += A_j^{-1} b^I) and Boundary (x^I = A_j^{-1} (b^I - A^{IB} x^B), x^I never read).
@@ -90,6 +91,8 @@ hipError_t launch_colour_pass_group(int dim, int k, int prec, int mode, int colo
 // parity; dim: the grid, all colours).  clear (ascending only): x holds anything and counts as 0.
 hipError_t launch_smooth_fused(const LevelGeom& g, int prec, bool additive, int span, bool reverse, bool clear,
                                const ColourPassMember* members, int n_members, hipStream_t st);
+hipError_t launch_additive_fused(const LevelGeom& g, int prec, int span, bool reverse, bool clear,
+                                 const ColourPassMember* members, int n_members, hipStream_t st);
 // The span of a step on a level; 0: one colour per launch.
 int fused_span(const LevelGeom& g, int prec, bool additive);
 // x = A_1^{-1} b on level 1 for every member, in FP64 arithmetic.
